@@ -260,8 +260,7 @@ Layout make_layout(const Shape& sh, int P, bool mixed)
     const bool fgt = sh.fgt_nc >= 0;
     const size_t fgt_boxes = fgt ? size_t(1) << (2 * sh.depth[0]) : 0;
     ly.fgt_a = take(sizeof(double) * fgt_boxes * P * P);
-    const size_t parts = fgt ? size_t(fgt_parts(P, sh.depth[0], sh.fgt_nc)) : 0;
-    ly.fgt_b = take(sizeof(double) * parts * fgt_boxes * P * P);
+    ly.fgt_b = take(sizeof(double) * fgt_boxes * P * P);
     ly.fgt_h = take(fgt ? sizeof(double) * size_t(2 * sh.fgt_nc + 1) * (2 * P - 1) : 0);
     // batched plans: what the table kernel reports of a call
     ly.counts = take(sizeof(int32_t) * 2);
@@ -566,7 +565,7 @@ hipError_t enqueue_all(fmm_plan_s* pl, int64_t n, const double* x, const double*
     if (pl->shape.fgt_nc >= 0) {   // Gauss transform: Hermite, Hermite to Taylor, Taylor evaluation
         mark(ST_UP);
         const int L = pl->shape.depth[0], nc = pl->shape.fgt_nc;
-        chk(launch_fgt(b, P, int(n), L, pl->prm.sigma, nc, fgt_parts(P, L, nc), int(m), u, v, st));
+        chk(launch_fgt(b, P, int(n), L, pl->prm.sigma, nc, int(m), u, v, st));
         for (int s2 = ST_M2L; s2 <= ST_COUNT; ++s2) mark(s2);
         return e;
     }

@@ -182,8 +182,8 @@ struct Buffers {
     double* t_sout;        // [P] 1 / l!
     // Gauss transform plans: Hermite and Taylor coefficients of every leaf
     // box, and the Hermite functions at the box offsets
-    double* fgt_a;         // [4^L][P][P]
-    double* fgt_b;         // [parts][4^L][P][P] (partial Taylor expansions, joined into part 0)
+    double* fgt_a;         // [4^L][P][P] Hermite coefficients, then the Taylor coefficients
+    double* fgt_b;         // [4^L][P][P] the Hermite coefficients translated along x
     double* fgt_h;         // [2 nc + 1][2P - 1]
 };
 
@@ -232,12 +232,10 @@ hipError_t launch_p2p_at(const Buffers& b, int P, int L, const NearKernel& nk, i
 // interaction lists of boxes [b0, b0 + cnt) of a depth-L tree into out[cnt][27]
 hipError_t launch_ilist(int L, int64_t b0, int64_t cnt, int32_t* out, hipStream_t st);
 // the fast Gauss transform of a single-instance plan (after the tree): P
-// Hermite terms per axis (8, 12 or 16), boxes within Chebyshev distance nc,
-// the range's rows split over `parts` partial expansions; evaluated at the
-// particles, or at the m sorted target points when m > 0
-hipError_t launch_fgt(const Buffers& b, int P, int n, int L, double sigma, int nc, int parts, int m, double* u,
-                      double* v, hipStream_t st);
-int fgt_parts(int P, int L, int nc);
+// Hermite terms per axis (8, 12 or 16), boxes within Chebyshev distance nc;
+// evaluated at the particles, or at the m sorted target points when m > 0
+hipError_t launch_fgt(const Buffers& b, int P, int n, int L, double sigma, int nc, int m, double* u, double* v,
+                      hipStream_t st);
 // h_n(d w / sqrt(delta)), |d| <= nc, n < 2P - 1, into out[(d + nc) (2P - 1) + n]
 void fgt_hermite_table(int P, int nc, double w_over_sd, double* out);
 // a[0..n) = b[0..n) = 0
