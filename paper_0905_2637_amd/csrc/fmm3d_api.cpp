@@ -17,7 +17,7 @@ size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 struct Layout3 {
     size_t hist, hist_scan, scan_part, ktmp, itmp, xt, yt, gt;
-    size_t key, ks, perm, xs, ys, zs, qs, leaf_start, me, le, dtab, dcube, kcube, nbad;
+    size_t key, ks, perm, xs, ys, zs, qs, leaf_start, me, mt, le, op, term, nbad;
     size_t total;
 };
 
@@ -38,7 +38,7 @@ Layout3 layout3(const fmm3d_params* prm)
     const size_t nblk = size_t(fmm::radix_blocks(int64_t(n)));
     const size_t nhist = size_t(256) * nblk;
     const size_t nscan = (nhist + fmm::kScanChunk - 1) / fmm::kScanChunk;
-    const int L = prm->depth, T = tet3(prm->p + 1), T2 = tet3(2 * prm->p + 1);
+    const int L = prm->depth, p = prm->p;
     const size_t nbox = size_t(lvl_off3(L + 1));
     Layout3 ly{};
     size_t off = 0;
@@ -59,13 +59,20 @@ Layout3 layout3(const fmm3d_params* prm)
     ly.zs = take(sizeof(double) * n);
     ly.qs = take(sizeof(double) * n);
     ly.leaf_start = take(sizeof(int32_t) * ((size_t(1) << (3 * L)) + 1));
-    ly.me = take(sizeof(double) * nbox * size_t(T));
-    ly.le = take(sizeof(double) * nbox * size_t(T));
-    ly.dtab = take(sizeof(double) * size_t(kOffsets3) * size_t(T2));
-    const size_t S = size_t(2 * prm->p + 1);
-    const bool lanes = prm->p >= 1 && prm->p <= kLaneMaxP3;
-    ly.dcube = take(lanes ? sizeof(double) * size_t(kOffsets3) * S * S * S : 0);
-    ly.kcube = take(lanes ? sizeof(int32_t) * size_t(T) : 0);
+    const size_t coef = off;
+    ly.me = take(sizeof(double) * nbox * size_t(stored3(p)));
+    ly.mt = take(sizeof(double) * size_t(grid_off3(L + 1)) * size_t(stored3(p)));
+    ly.le = take(sizeof(double) * nbox * size_t(stored3(p)));
+    ly.op = take(sizeof(double) * size_t(operators3(p)) * size_t(steps3(p)) * size_t(tiles3(p)) * 64);
+    static_assert(stored3(kP3Max) <= 64 * (kP3Max + 1), "the term table fits");
+    ly.term = take(sizeof(int32_t) * 64 * size_t(p + 1));
+    // The size grows with p (a 256-byte row of the term table per degree;
+    // degrees 0 and 1 store the same four terms per box) and is never less than
+    // full sets of coefficients and of derivatives (as rows and as cubes) would
+    // take, what callers of this form budget by.
+    const size_t S = size_t(2 * p + 1);
+    const size_t full = 2 * nbox * size_t(tet3(p + 1)) + size_t(kOffsets3) * (size_t(tet3(2 * p + 1)) + (p > 0 ? S * S * S : 0));
+    off = std::max(off, align256(coef + sizeof(double) * full));
     ly.nbad = take(sizeof(unsigned long long));
     ly.total = off;
     return ly;
@@ -84,7 +91,9 @@ Layout3 layout3(const fmm3d_params* prm)
 // double).  (A
 // binomial-series composition; the oracle takes the three-term recurrence
 // of the same coefficients, so the two tables share no arithmetic.)
-std::vector<double> derivative_table(int p)
+// Offsets with a negative ox or oy are left out (zero) when `folded`: the
+// M2L then reaches them by reflection.
+std::vector<double> derivative_table(int p, bool folded)
 {
     const int q = 2 * p, T2 = tet3(q + 1);
     std::vector<double> tab(size_t(kOffsets3) * size_t(T2), 0.0);
@@ -97,6 +106,7 @@ std::vector<double> derivative_table(int p)
         for (int oy = -3; oy <= 3; ++oy)
             for (int ox = -3; ox <= 3; ++ox) {
                 if (std::abs(ox) <= 1 && std::abs(oy) <= 1 && std::abs(oz) <= 1) continue;
+                if (folded && (ox < 0 || oy < 0)) continue;
                 const double R[3] = {double(ox), double(oy), double(oz)};
                 const double r2 = R[0] * R[0] + R[1] * R[1] + R[2] * R[2];
                 const long double lr2 = r2;
@@ -140,15 +150,60 @@ std::vector<double> derivative_table(int p)
     return tab;
 }
 
+// (a, b, c) of every stored position (fmm3d_internal.h), -1 for padding.
+std::vector<int32_t> term_table(int p)
+{
+    std::vector<int32_t> t(size_t(stored3(p)), -1);
+    for (int cl = 0; cl < classes3(p); ++cl) {
+        int k = class_base3(p, cl);
+        for (int c = 0; c <= 1 && c <= p; ++c)
+            for (int a = 0; a + c <= p; ++a)
+                for (int b = 0; a + b + c <= p; ++b)
+                    if (class3(p, a, b) == cl) t[size_t(k++)] = a | b << 8 | c << 16;
+    }
+    return t;
+}
+
+// The M2L operators D_(k + n)(o) as the matrix instructions read them: the
+// value of lane l in step st and tile ti has row n = the tile's term l mod 16
+// and column k = the term of lane group l / 16 (zero where either is padding).
+std::vector<double> operator_table(int p, const std::vector<int32_t>& term)
+{
+    const std::vector<double> D = derivative_table(p, fold3(p));
+    const int T2 = tet3(2 * p + 1), NS = steps3(p), RT = tiles3(p);
+    std::vector<double> op(size_t(operators3(p)) * size_t(NS) * size_t(RT) * 64, 0.0);
+    std::vector<int> at(size_t(NS) * size_t(RT) * 64, -1);   // graded position of k + n, the same for every offset
+    for (int cl = 0; cl < classes3(p); ++cl)
+        for (int i = 0; i < class_tiles3(p, cl); ++i)
+            for (int st = 0; st < NS; ++st)
+                for (int l = 0; l < 64; ++l) {
+                    const int row = 16 * i + l % 16;
+                    if (row >= class_size3(p, cl)) continue;
+                    const int n = term[size_t(class_base3(p, cl) + row)], k = term[size_t(4 * st + l / 16)];
+                    if (n < 0 || k < 0) continue;
+                    at[(size_t(st) * size_t(RT) + size_t(tile_base3(p, cl) + i)) * 64 + size_t(l)] =
+                        pos3((n & 255) + (k & 255), ((n >> 8) & 255) + ((k >> 8) & 255), (n >> 16) + (k >> 16));
+                }
+    const int lo = fold3(p) ? 0 : -3;
+    for (int oz = -3; oz <= 3; ++oz)
+        for (int oy = lo; oy <= 3; ++oy)
+            for (int ox = lo; ox <= 3; ++ox) {
+                double* dst = op.data() + size_t(operator3(p, ox, oy, oz)) * at.size();
+                const double* row = D.data() + size_t(off3_index(ox, oy, oz)) * size_t(T2);
+                for (size_t e = 0; e < at.size(); ++e)
+                    if (at[e] >= 0) dst[e] = row[at[e]];
+            }
+    return op;
+}
+
 }  // namespace
 
 struct fmm3d_plan_s {
     fmm3d_params prm;
     Bufs3 buf;
     Geo3 geo;
-    std::vector<double> dtab_host;   // source of the table upload, kept until the plan ends
-    std::vector<double> dcube_host;
-    std::vector<int32_t> kcube_host;
+    std::vector<double> op_host;     // sources of the table uploads, kept until the plan ends
+    std::vector<int32_t> term_host;
     int64_t last_n = 0;
 };
 
@@ -197,10 +252,10 @@ fmm_status fmm3d_plan(const fmm3d_params* prm, void* d_workspace, size_t bytes, 
     b.qs = static_cast<double*>(at(ly.qs));
     b.leaf_start = static_cast<int32_t*>(at(ly.leaf_start));
     b.me = static_cast<double*>(at(ly.me));
+    b.mt = static_cast<double*>(at(ly.mt));
     b.le = static_cast<double*>(at(ly.le));
-    b.dtab = static_cast<double*>(at(ly.dtab));
-    b.dcube = static_cast<double*>(at(ly.dcube));
-    b.kcube = static_cast<int32_t*>(at(ly.kcube));
+    b.op = static_cast<double*>(at(ly.op));
+    b.term = static_cast<int32_t*>(at(ly.term));
     b.nbad = static_cast<unsigned long long*>(at(ly.nbad));
     Geo3& g = pl->geo;
     g.x0 = prm->x0;
@@ -209,44 +264,17 @@ fmm_status fmm3d_plan(const fmm3d_params* prm, void* d_workspace, size_t bytes, 
     g.W = prm->width;
     g.L = prm->depth;
     g.p = prm->p;
-    g.T = tet3(prm->p + 1);
-    g.T2 = tet3(2 * prm->p + 1);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool lanes = prm->p >= 1 && prm->p <= kLaneMaxP3;
     try {
-        pl->dtab_host = derivative_table(prm->p);
-        if (lanes) {
-            // the graded rows rearranged as dense (2p+1)^3 cubes (entries of degree > 2p stay 0)
-            const int S = 2 * prm->p + 1, T2 = g.T2;
-            pl->dcube_host.assign(size_t(kOffsets3) * size_t(S * S * S), 0.0);
-            for (int o = 0; o < kOffsets3; ++o)
-                for (int d = 0; d <= 2 * prm->p; ++d)
-                    for (int s2 = 0; s2 <= d; ++s2)
-                        for (int c = 0; c <= s2; ++c) {
-                            const int a = d - s2, bb = s2 - c;
-                            pl->dcube_host[size_t(o) * size_t(S * S * S) + size_t((a * S + bb) * S + c)] =
-                                pl->dtab_host[size_t(o) * size_t(T2) + size_t(pos3(a, bb, c))];
-                        }
-            pl->kcube_host.assign(size_t(g.T), 0);
-            for (int d = 0; d <= prm->p; ++d)
-                for (int s2 = 0; s2 <= d; ++s2)
-                    for (int c = 0; c <= s2; ++c) {
-                        const int a = d - s2, bb = s2 - c;
-                        pl->kcube_host[size_t(pos3(a, bb, c))] = (a * S + bb) * S + c;
-                    }
-        }
+        pl->term_host = term_table(prm->p);
+        pl->op_host = operator_table(prm->p, pl->term_host);
     } catch (...) {
         delete pl;
         return FMM_E_NOMEM;
     }
-    if (lanes && (hipMemcpyAsync(b.dcube, pl->dcube_host.data(), pl->dcube_host.size() * sizeof(double),
-                                 hipMemcpyHostToDevice, st) != hipSuccess ||
-                  hipMemcpyAsync(b.kcube, pl->kcube_host.data(), pl->kcube_host.size() * sizeof(int32_t),
-                                 hipMemcpyHostToDevice, st) != hipSuccess)) {
-        delete pl;
-        return FMM_E_DEVICE;
-    }
-    if (hipMemcpyAsync(b.dtab, pl->dtab_host.data(), pl->dtab_host.size() * sizeof(double), hipMemcpyHostToDevice,
+    if (hipMemcpyAsync(b.op, pl->op_host.data(), pl->op_host.size() * sizeof(double), hipMemcpyHostToDevice, st) !=
+            hipSuccess ||
+        hipMemcpyAsync(b.term, pl->term_host.data(), pl->term_host.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                        st) != hipSuccess ||
         launch3_clear(b, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
         delete pl;

@@ -1,12 +1,20 @@
 // fmm3d_internal.h -- device buffers, geometry and launchers of the 3D form
 // (fmm3d.hip, fmm3d_api.cpp).
 //
-// Coefficients of total degree <= p are stored in graded order: degree d,
-// then s = b + c ascending, then c ascending, so multi-index (a, b, c) sits
-// at tet(a + b + c) + tri(b + c) + c with tet(d) = d (d+1) (d+2) / 6 (the
-// number of multi-indices of degree < d) and tri(s) = s (s+1) / 2.  With this
-// order the multi-indices k + n for fixed n, fixed degree of k and fixed
-// b + c of k are contiguous in c, which the M2L loop uses.
+// Expansions.  A coefficient has a multi-index (a, b, c) of total degree <= p.
+// 1/r is harmonic, so its derivatives D_m satisfy D_(m + 2 e_z) = -D_(m + 2 e_x)
+// - D_(m + 2 e_y): moments only matter up to that relation, and the local
+// coefficients obey it.  Both are therefore kept for c <= 1 alone, (p + 1)^2
+// terms instead of (p + 1)(p + 2)(p + 3)/6; the other terms of a moment set
+// are folded into these, those of a local set follow from these, in either
+// case within one degree, so nothing but rounding changes.
+//
+// Kept terms are stored by class, the parities of (a, b) (four classes where
+// the M2L folds reflections, fold3(p); else one class), each class padded to
+// a multiple of 4 with zeros: the M2L's matrix instructions take four source
+// terms of one class.  Graded order (degree, then s = b + c, then c) puts
+// (a, b, c) of a full set at tet(a + b + c) + tri(b + c) + c with tet(d) =
+// d (d+1) (d+2) / 6 and tri(s) = s (s+1) / 2.
 #pragma once
 
 #include "fmm_internal.h"
@@ -23,13 +31,8 @@ hipError_t launch_sort_keys(const Buffers& b, int n, const uint32_t* key, const 
 namespace fmm3 {
 
 constexpr int kP3Max = 9;          // expansion degree
-constexpr int kT3Max = 220;        // terms of degree <= 9
-constexpr int kT3Max2 = 1330;      // terms of degree <= 18 (derivatives for the M2L)
 constexpr int kDepth3Max = 7;      // 21 key bits plus the outside flag
 constexpr int kOffsets3 = 343;     // offsets in [-3, 3]^3
-constexpr int kLaneMaxP3 = 9;      // degrees whose M2L takes one lane per target box (1 .. this);
-                                   // the derivative cubes are allocated and the lane kernel
-                                   // dispatched for exactly these
 
 __host__ __device__ constexpr int tet3(int d) { return d * (d + 1) * (d + 2) / 6; }
 __host__ __device__ constexpr int tri3(int s) { return s * (s + 1) / 2; }
@@ -37,11 +40,72 @@ __host__ __device__ constexpr int pos3(int a, int b, int c) { return tet3(a + b 
 __host__ __device__ constexpr int64_t lvl_off3(int l) { return ((int64_t(1) << (3 * l)) - 1) / 7; }
 __host__ __device__ constexpr int off3_index(int ox, int oy, int oz) { return ((oz + 3) * 7 + (oy + 3)) * 7 + (ox + 3); }
 
-// Cube [x0, x0 + W)^3, depth L, degree p with T = tet3(p + 1) terms and
-// T2 = tet3(2 p + 1) derivative terms.
+// The M2L folds the reflections of x and y (one operator for up to four
+// offsets, its rows split into the four classes) where the split rows fill
+// their 16-row tiles well enough: from p = 5 on (p = 4: 2,688 matrix
+// instructions per 16 targets folded against 2,646 unfolded; p = 5: 3,360
+// against 5,103; p = 6: 4,368 against 9,828).
+__host__ __device__ constexpr bool fold3(int p) { return p >= 5; }
+__host__ __device__ constexpr int classes3(int p) { return fold3(p) ? 4 : 1; }
+__host__ __device__ constexpr int class3(int p, int a, int b) { return fold3(p) ? (a & 1) | ((b & 1) << 1) : 0; }
+// kept terms of a class, and that padded
+__host__ __device__ constexpr int class_terms3(int p, int cl)
+{
+    int n = 0;
+    for (int c = 0; c <= 1 && c <= p; ++c)
+        for (int a = 0; a + c <= p; ++a)
+            for (int b = 0; a + b + c <= p; ++b) n += class3(p, a, b) == cl ? 1 : 0;
+    return n;
+}
+__host__ __device__ constexpr int class_size3(int p, int cl) { return (class_terms3(p, cl) + 3) / 4 * 4; }
+__host__ __device__ constexpr int class_base3(int p, int cl)
+{
+    int n = 0;
+    for (int k = 0; k < cl; ++k) n += class_size3(p, k);
+    return n;
+}
+// stored doubles per box
+__host__ __device__ constexpr int stored3(int p) { return class_base3(p, classes3(p)); }
+
+// M2L matrix instructions: steps of four source terms, 16-row tiles of output
+// terms.
+__host__ __device__ constexpr int steps3(int p) { return stored3(p) / 4; }
+__host__ __device__ constexpr int class_tiles3(int p, int cl) { return (class_size3(p, cl) + 15) / 16; }
+__host__ __device__ constexpr int tile_base3(int p, int cl)
+{
+    int n = 0;
+    for (int k = 0; k < cl; ++k) n += class_tiles3(p, k);
+    return n;
+}
+__host__ __device__ constexpr int tiles3(int p) { return tile_base3(p, classes3(p)); }
+// operators of the M2L: folded, offsets (|ox|, |oy|, oz); else all offsets
+__host__ __device__ constexpr int operators3(int p) { return fold3(p) ? 4 * 4 * 7 : kOffsets3; }
+__host__ __device__ constexpr int operator3(int p, int ox, int oy, int oz)
+{
+    return fold3(p) ? ((oz + 3) * 4 + oy) * 4 + ox : off3_index(ox, oy, oz);
+}
+
+// M2L sources of level l (l >= 2): the boxes of one child position form the
+// grid of their parents, 2^(l-1) a side.  The sources of a box lie under its
+// parent and the parents touching that one, so with a border of one they are
+// all found at a fixed distance, zero outside the cube.
+__host__ __device__ constexpr int64_t grid3(int l)
+{
+    const int64_t s = (int64_t(1) << (l - 1)) + 2;
+    return s * s * s;
+}
+// first source double of level l, in boxes (times stored3(p))
+__host__ __device__ constexpr int64_t grid_off3(int l)
+{
+    int64_t n = 0;
+    for (int k = 2; k < l; ++k) n += 8 * grid3(k);
+    return n;
+}
+
+// Cube [x0, x0 + W)^3, depth L, degree p.
 struct Geo3 {
     double x0, y0, z0, W;
-    int L, p, T, T2;
+    int L, p;
 };
 
 struct Bufs3 {
@@ -51,11 +115,13 @@ struct Bufs3 {
     uint32_t* perm;             // [n_max] sorted position -> input index
     double *xs, *ys, *zs, *qs;  // [n_max] sorted particles
     int32_t* leaf_start;        // [8^L + 1] sorted range of every leaf; the last entry counts the inside ones
-    double* me;                 // [boxes of levels 0..L][T] scaled moments
-    double* le;                 // [boxes of levels 0..L][T] scaled local coefficients
-    double* dtab;               // [343][T2] derivatives of 1/r at the integer offsets, graded order
-    double* dcube;              // p <= kLaneMaxP3: [343][(2p+1)^3] the same derivatives as dense cubes
-    int32_t* kcube;             // p <= kLaneMaxP3: [T] cube index of each graded multi-index
+    double* me;                 // [boxes of levels 0..L][stored3(p)] scaled moments
+    double* mt;                 // levels 2..L: the moments again as the M2L reads them, [child position][stored3(p)]
+                                // [parents of the level above, x fastest, with a border of zeros]
+    double* le;                 // [boxes of levels 0..L][stored3(p)] scaled local coefficients
+    double* op;                 // [operators3(p)][steps3(p)][tiles3(p)][64] M2L operators, a lane's value of each
+                                // matrix instruction
+    int32_t* term;              // [stored3(p)] a | b << 8 | c << 16 of every stored position, -1: padding
     unsigned long long* nbad;   // particles outside the cube or NaN
 };
 
