@@ -65,14 +65,30 @@ k_bbox_partial(int n, const double* __restrict__ x, const double* __restrict__ y
 }
 
 // Bounding square: x0 = min x, y0 = min y, W = the larger extent, 1 if the
-// particles span nothing or the extent is not finite.
-__global__ void k_bbox_final(int nblk, const double* __restrict__ part, int L, Domain* dom)
+// particles span nothing or the extent is not finite.  One workgroup, a
+// partial box per thread: 4 us (39 us for one thread walking 256 of them).
+__global__ void __launch_bounds__(256) k_bbox_final(int nblk, const double* __restrict__ part, int L, Domain* dom)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
     double xmin = INFINITY, xmax = -INFINITY, ymin = INFINITY, ymax = -INFINITY;
-    for (int b = 0; b < nblk; ++b) {
+    for (int b = threadIdx.x; b < nblk; b += 256) {
         xmin = fmin(xmin, part[4 * b + 0]); xmax = fmax(xmax, part[4 * b + 1]);
         ymin = fmin(ymin, part[4 * b + 2]); ymax = fmax(ymax, part[4 * b + 3]);
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        xmin = fmin(xmin, __shfl_xor(xmin, d, 64)); xmax = fmax(xmax, __shfl_xor(xmax, d, 64));
+        ymin = fmin(ymin, __shfl_xor(ymin, d, 64)); ymax = fmax(ymax, __shfl_xor(ymax, d, 64));
+    }
+    __shared__ double sh[4][4];
+    if (__lane_id() == 0) {
+        double* w = sh[threadIdx.x >> 6];
+        w[0] = xmin; w[1] = xmax; w[2] = ymin; w[3] = ymax;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < 4; ++k) {
+        xmin = fmin(xmin, sh[k][0]); xmax = fmax(xmax, sh[k][1]);
+        ymin = fmin(ymin, sh[k][2]); ymax = fmax(ymax, sh[k][3]);
     }
     double w = xmax - xmin;
     if (ymax - ymin > w) w = ymax - ymin;
@@ -591,7 +607,7 @@ hipError_t launch_domain(const Buffers& b, int n, const double* x, const double*
     hipLaunchKernelGGL(k_bbox_partial, dim3(kBBoxBlocks), dim3(256), 0, st, n, x, y, b.bbox);
     if (m > 0)   // target points: their partial boxes follow the particles'
         hipLaunchKernelGGL(k_bbox_partial, dim3(kBBoxBlocks), dim3(256), 0, st, m, tx, ty, b.bbox + 4 * kBBoxBlocks);
-    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(64), 0, st, m > 0 ? 2 * kBBoxBlocks : kBBoxBlocks, b.bbox, L,
+    hipLaunchKernelGGL(k_bbox_final, dim3(1), dim3(256), 0, st, m > 0 ? 2 * kBBoxBlocks : kBBoxBlocks, b.bbox, L,
                        &b.inst[0].dom);
     return hipGetLastError();
 }
