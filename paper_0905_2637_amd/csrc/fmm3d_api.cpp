@@ -36,16 +36,15 @@ Layout3 layout3(const fmm3d_params* prm)
 {
     const size_t n = size_t(prm->n_max > 0 ? prm->n_max : 1);
     const size_t nblk = size_t(fmm::radix_blocks(int64_t(n)));
-    const size_t nhist = size_t(256) * nblk;
-    const size_t nscan = (nhist + fmm::kScanChunk - 1) / fmm::kScanChunk;
+    const size_t nhist = size_t(fmm::kHistDigits) * nblk;
     const int L = prm->depth, p = prm->p;
     const size_t nbox = size_t(lvl_off3(L + 1));
     Layout3 ly{};
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
     ly.hist = take(sizeof(int32_t) * nhist);
-    ly.hist_scan = take(sizeof(int32_t) * (nhist + 1));
-    ly.scan_part = take(sizeof(int32_t) * (nscan + 1));
+    ly.hist_scan = take(sizeof(int32_t) * nhist);
+    ly.scan_part = take(sizeof(int32_t) * fmm::kHistDigits);
     ly.ktmp = take(sizeof(uint32_t) * n);
     ly.itmp = take(sizeof(uint32_t) * n);
     ly.xt = take(sizeof(double) * n);

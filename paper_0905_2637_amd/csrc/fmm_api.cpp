@@ -213,8 +213,6 @@ Layout make_layout(const Shape& sh, int P, bool mixed)
     const size_t m = size_t(sh.m_cap);
     const size_t nm = std::max(n, m);   // the radix temporaries serve both point sets
     const size_t nblk = size_t(radix_blocks(int64_t(nm)));
-    const size_t nhist = size_t(256) * nblk;
-    const size_t nscan = (nhist + kScanChunk - 1) / kScanChunk;
     Layout ly{};
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes); return o; };
@@ -223,9 +221,9 @@ Layout make_layout(const Shape& sh, int P, bool mixed)
     ly.bad_blk = take(sizeof(int32_t) * nblk);
     ly.bbox = take(sizeof(double) * 8 * kBBoxBlocks);
     ly.leaf_start = take(sizeof(int32_t) * size_t(sh.leaf_entries));
-    ly.hist = take(sizeof(int32_t) * nhist);
-    ly.hist_scan = take(sizeof(int32_t) * (nhist + 1));   // + the grand total
-    ly.scan_part = take(sizeof(int32_t) * (nscan + 1));
+    ly.hist = take(hist_bytes(int64_t(nm), sh.batched ? 0 : sh.n_inst, sh.key_bits));
+    ly.hist_scan = take(sizeof(int32_t) * kHistDigits * nblk);
+    ly.scan_part = take(sizeof(int32_t) * kHistDigits);
     ly.key = take(sizeof(uint32_t) * n);
     ly.ksorted = take(sizeof(uint32_t) * n);
     ly.perm = take(sizeof(uint32_t) * n);
@@ -641,6 +639,8 @@ fmm_status make_plan(const fmm_params* prm, Shape&& sh, bool batch, void* d_work
     b.inst = reinterpret_cast<Inst*>(base + ly.inst);
     b.n_inst = pl->shape.n_inst;
     b.key_shift = 2 * pl->shape.Lmax;
+    b.small_sort = small_sort(std::max(pl->shape.n_cap, pl->shape.m_cap), pl->shape.batched ? 0 : pl->shape.n_inst,
+                              pl->shape.key_bits);
     pl->d_tables = reinterpret_cast<int32_t*>(base + ly.tables);
     b.bad_blk = reinterpret_cast<int32_t*>(base + ly.bad_blk);
     b.bbox = reinterpret_cast<double*>(base + ly.bbox);

@@ -146,9 +146,10 @@ struct Buffers {
     int32_t* bad_blk;      // [radix blocks] particles outside the domain / NaN, per tile
     double* bbox;          // [8 * kBBoxBlocks] partial bounding boxes (particles, then target points)
     int32_t* leaf_start;   // [sum (4^L_i + 1)] sorted ranges of every leaf of every instance
-    int32_t* hist;         // [256 * radix blocks] digit-major tile histograms
-    int32_t* hist_scan;    // [256 * radix blocks + 1] exclusive scan of hist, then the total
-    int32_t* scan_part;    // [scan chunks + 1]
+    bool small_sort;       // the particles (and target points) sort in one pass over the whole key
+    int32_t* hist;         // [256 * radix blocks] digit-major tile histograms (hist_bytes)
+    int32_t* hist_scan;    // [256 * radix blocks] exclusive scans of its rows
+    int32_t* scan_part;    // [256] and the rows' totals
     uint32_t* key;         // [n_max] instance and leaf key per input particle
     uint32_t* ksorted;     // [n_max] sorted keys
     uint32_t* perm;        // [n_max] sorted position -> input index
@@ -187,13 +188,15 @@ struct Buffers {
     double* fgt_h;         // [2 nc + 1][2P - 1]
 };
 
-// Chunk of the histogram scan handled by one workgroup.
-constexpr int kScanChunk = 2048;
-
 // Radix sort geometry (fmm_tree.hip): passes of 8-bit digits over the key
 // bits, and workgroup tiles of 4096 keys.
 int radix_passes(int key_bits);
 int64_t radix_blocks(int64_t n);
+// whether a plan of this capacity sorts in one pass over the whole key, and
+// the bytes of its histograms
+bool small_sort(int64_t n_cap, int n_inst, int key_bits);
+size_t hist_bytes(int64_t n_cap, int n_inst, int key_bits);
+constexpr int kHistDigits = 256;
 
 // ---- launchers (each enqueues on `st` and returns the launch status) -------
 

@@ -24,6 +24,8 @@
 // ~16 records per digit and tile) and no random gather follows: the last pass
 // writes the sorted arrays the later stages read, plus the mixed-precision
 // FP32 leaf-relative record.  The first histogram pass computes the keys.
+#include <algorithm>
+
 #include "fmm_device.h"
 
 namespace fmm {
@@ -135,64 +137,44 @@ __device__ __forceinline__ int wave_incl_scan(int v)
     return v;
 }
 
-// Exclusive scan over a 256-thread block; *total gets the block sum.
-__device__ __forceinline__ int block_excl_scan(int v, int* total)
+// Histogram table of a radix pass, digit-major [256][nblk]: one workgroup per
+// digit scans its row into out (exclusive) and writes the digit's total; the
+// scatter turns the 256 totals into the digits' starts itself.  A wavefront
+// takes a run of the row, 64 tiles a round.  Latency-bound: 4.7 us a pass on
+// 256 tiles and 14 us on 16,384, against 9.5 and 30 us for a two-level scan
+// of the whole table by two kernels.
+constexpr int kRowScanThreads = 1024;
+constexpr int kRowScanWaves = kRowScanThreads / 64;
+
+__global__ void __launch_bounds__(kRowScanThreads)
+k_scan_rows(int nblk, const int32_t* __restrict__ in, int32_t* __restrict__ out, int32_t* __restrict__ total)
 {
-    __shared__ int wsum[5];
+    __shared__ int wsum[kRowScanWaves];
     const int lane = __lane_id(), w = threadIdx.x >> 6;
-    const int inc = wave_incl_scan(v);
-    if (lane == 63) wsum[w] = inc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int k = 0; k < 4; ++k) { const int t = wsum[k]; wsum[k] = run; run += t; }
-        wsum[4] = run;
-    }
-    __syncthreads();
-    const int r = inc - v + wsum[w];
-    *total = wsum[4];
-    __syncthreads();
-    return r;
-}
-
-constexpr int kScanPerThread = kScanChunk / 256;
-
-__global__ void __launch_bounds__(256)
-k_scan_reduce(int64_t m, const int32_t* __restrict__ in, int32_t* __restrict__ part)
-{
-    const int64_t base = int64_t(blockIdx.x) * kScanChunk + int64_t(threadIdx.x) * kScanPerThread;
+    const int run_tiles = ((nblk + kRowScanThreads - 1) / kRowScanThreads) * 64;
+    const int b0 = min(nblk, w * run_tiles), b1 = min(nblk, b0 + run_tiles);
+    const int32_t* src = in + int64_t(blockIdx.x) * nblk;
+    int32_t* dst = out + int64_t(blockIdx.x) * nblk;
     int s = 0;
+#pragma unroll 8
+    for (int b = b0 + lane; b < b1; b += 64) s += src[b];
+    s = wave_incl_scan(s);
+    if (lane == 63) wsum[w] = s;
+    __syncthreads();
+    int run = 0, all = 0;
 #pragma unroll
-    for (int k = 0; k < kScanPerThread; ++k) s += (base + k < m) ? in[base + k] : 0;
-    int total;
-    block_excl_scan(s, &total);
-    if (threadIdx.x == 0) part[blockIdx.x] = total;
-}
-
-// Second level: every workgroup adds up the chunk sums before its own (there
-// are few: n / 4096 tiles x 256 digits / 2048 per chunk), scans its chunk
-// and the last one writes the grand total to out[m].
-__global__ void __launch_bounds__(256)
-k_scan_down(int64_t m, int nb, const int32_t* __restrict__ in, const int32_t* __restrict__ part,
-            int32_t* __restrict__ out)
-{
-    int pre = 0;
-    for (int i = threadIdx.x; i < int(blockIdx.x); i += 256) pre += part[i];
-    int before;
-    block_excl_scan(pre, &before);          // the block sum of pre: every chunk before this one
-    const int64_t base = int64_t(blockIdx.x) * kScanChunk + int64_t(threadIdx.x) * kScanPerThread;
-    int v[kScanPerThread];
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanPerThread; ++k) { v[k] = (base + k < m) ? in[base + k] : 0; s += v[k]; }
-    int total;
-    int run = block_excl_scan(s, &total) + before;
-#pragma unroll
-    for (int k = 0; k < kScanPerThread; ++k) {
-        if (base + k < m) out[base + k] = run;
-        run += v[k];
+    for (int k = 0; k < kRowScanWaves; ++k) {
+        run += k < w ? wsum[k] : 0;
+        all += wsum[k];
     }
-    if (blockIdx.x == nb - 1 && threadIdx.x == 0) out[m] = before + total;
+#pragma unroll 4
+    for (int c = b0; c < b1; c += 64) {
+        const int b = c + lane, v = b < b1 ? src[b] : 0;
+        const int inc = wave_incl_scan(v);
+        if (b < b1) dst[b] = run + inc - v;
+        run += __builtin_amdgcn_readlane(inc, 63);
+    }
+    if (threadIdx.x == 0) total[blockIdx.x] = all;
 }
 
 // ---------------------------------------------------------------------------
@@ -201,6 +183,8 @@ k_scan_down(int64_t m, int nb, const int32_t* __restrict__ in, const int32_t* __
 
 constexpr int kRadixBins = 256;
 constexpr int kRadixTile = 4096;   // keys per workgroup
+constexpr int kSmallTiles = 64;
+constexpr int kSmallKeyBits = 12;
 
 // Instance owning input particle i (its particles are [part_off, next part_off)).
 __device__ __forceinline__ int particle_inst(const Inst* __restrict__ inst, int n_inst, int64_t i)
@@ -345,7 +329,8 @@ struct Records {
 // the wavefronts, giving every record its position in the digit-sorted tile.
 // Phase B stages each array through LDS in that order, so that consecutive
 // threads write consecutive addresses of each digit's run (offs[d * nblk +
-// block] is where the tile's run of digit d starts): whole cache lines
+// block] is where the tile's run starts among digit d, total[d] the count of
+// digit d): whole cache lines
 // instead of scattered 8-byte writes.
 // iin == nullptr means the identity (first pass).  pk != nullptr (last pass,
 // mixed precision) also writes the FP32 leaf-relative record
@@ -354,8 +339,8 @@ template <int TPB>
 __global__ void __launch_bounds__(TPB)
 k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__ iin,
            const double* __restrict__ xin, const double* __restrict__ yin, const double* __restrict__ gin,
-           int shift, int nblk, const int32_t* __restrict__ hist, const int32_t* __restrict__ offs, Records out,
-           float4* __restrict__ pk, const Inst* __restrict__ inst, int key_shift, const int32_t* __restrict__ n_dev)
+           int shift, int nblk, const int32_t* __restrict__ hist, const int32_t* __restrict__ offs,
+           const int32_t* __restrict__ total, Records out, float4* __restrict__ pk, const Inst* __restrict__ inst, int key_shift, const int32_t* __restrict__ n_dev)
 {
     if (n_dev) n = *n_dev;
     constexpr int kScatterThreads = TPB;
@@ -364,7 +349,7 @@ k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__
     constexpr bool kUpFront = kPerThread <= 4;
     __shared__ int gbase[kRadixBins];      // global start of this tile's run of digit d
     __shared__ int tstart[kRadixBins];     // start of digit d in the sorted tile
-    __shared__ int wsum[4];
+    __shared__ int wsum[2][4];
     __shared__ int whist[kScatterWaves][kRadixBins];   // per wavefront: records of digit d so far
     __shared__ uint32_t sk[kRadixTile];
     __shared__ double sv[kRadixTile];
@@ -379,13 +364,19 @@ k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__
     constexpr int kWaveKeys = kRadixTile / kScatterWaves;
 
     // the tile's histogram (one digit per thread of the first 256) scanned
-    // into tstart; the first four wavefronts hold it
-    int hv = 0, hinc = 0;
+    // into tstart, the digits' totals into their starts in the output; the
+    // first four wavefronts hold both
+    int hv = 0, hinc = 0, go = 0, tv = 0, tinc = 0;
     if (tid < kRadixBins) {
         hv = hist[int64_t(tid) * nblk + blk];
-        gbase[tid] = offs[int64_t(tid) * nblk + blk];
+        go = offs[int64_t(tid) * nblk + blk];
+        tv = total[tid];
         hinc = wave_incl_scan(hv);
-        if (lane == 63) wsum[w] = hinc;
+        tinc = wave_incl_scan(tv);
+        if (lane == 63) {
+            wsum[0][w] = hinc;
+            wsum[1][w] = tinc;
+        }
     }
 #pragma unroll
     for (int e = tid; e < kScatterWaves * kRadixBins; e += kScatterThreads) (&whist[0][0])[e] = 0;
@@ -409,10 +400,14 @@ k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__
     }
     __syncthreads();
     if (tid < kRadixBins) {
-        int before = 0;
+        int before = 0, start = 0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) before += q < w ? wsum[q] : 0;
+        for (int q = 0; q < 4; ++q) {
+            before += q < w ? wsum[0][q] : 0;
+            start += q < w ? wsum[1][q] : 0;
+        }
         tstart[tid] = before + hinc - hv;
+        gbase[tid] = start + tinc - tv + go;
     }
 
     // rank within the wavefront, round after round (input order): equal
@@ -527,6 +522,278 @@ k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__
     }
 }
 
+// ---------------------------------------------------------------------------
+// Small sorts: one pass over the whole key
+// ---------------------------------------------------------------------------
+//
+// Up to kSmallTiles tiles of a single instance with at most kSmallKeyBits key
+// bits sort by one counting pass over the whole key: a tile's counts per leaf
+// are 16-bit (a tile has 4096 keys), one row per tile, and every scatter
+// workgroup adds up the rows itself, which also gives the leaf ranges.  At
+// these sizes a kernel costs its latency: three kernels (one for a single
+// tile) replace four per digit and the leaf-range kernel.  Tree of 4,096 particles, 8 key bits: 11
+// us instead of 23; 100,000, 10 bits: 22 instead of 56; 200,000, 12 bits: 32
+// instead of 60.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / 64;
+constexpr int kSmallPer = kRadixTile / kSmallThreads;
+
+// Sort key of a particle of the only instance: its leaf.
+__device__ __forceinline__ uint32_t leaf_key(double x, double y, const Domain& d, int L, bool& bad)
+{
+    const int side = 1 << L;
+    bad = !(d.W <= kMaxWidth);             // a bounding square wider than the limit
+    const int a = axis_box(x, d.x0, d.s, side, bad);
+    const int b = axis_box(y, d.y0, d.s, side, bad);
+    return morton(uint32_t(a), uint32_t(b));
+}
+
+// FP32 record (x - c, y - c) / w_L, gamma of leaf k's centre c.
+__device__ __forceinline__ float4 leaf_record(uint32_t k, double x, double y, double g, const Domain& d, int L)
+{
+    const double w = ldexp(d.W, -L);
+    const double cx = d.x0 + (double(morton_x(k)) + 0.5) * w;
+    const double cy = d.y0 + (double(morton_y(k)) + 0.5) * w;
+    return make_float4(float((x - cx) * d.s), float((y - cy) * d.s), float(g), 0.0f);
+}
+
+// Keys, out-of-domain count and leaf counts of every tile.
+__global__ void __launch_bounds__(kSmallThreads)
+k_small_keys(int n, const double* __restrict__ x, const double* __restrict__ y, const Inst* __restrict__ inst,
+             uint32_t* __restrict__ key, uint16_t* __restrict__ hist, int32_t* __restrict__ bad_blk)
+{
+    extern __shared__ int h[];
+    __shared__ int nbad;
+    const int L = inst[0].L, bins = 1 << (2 * L), tid = threadIdx.x;
+    const Domain d = inst[0].dom;
+    const int base = int(blockIdx.x) * kRadixTile;
+    if (tid == 0) nbad = 0;
+    for (int e = tid; e < bins; e += kSmallThreads) h[e] = 0;
+    double xv[kSmallPer], yv[kSmallPer];
+#pragma unroll
+    for (int r = 0; r < kSmallPer; ++r) {
+        const int i = min(n - 1, base + r * kSmallThreads + tid);
+        xv[r] = x[i];
+        yv[r] = y[i];
+    }
+    __syncthreads();
+    int mybad = 0;
+#pragma unroll
+    for (int r = 0; r < kSmallPer; ++r) {
+        const int i = base + r * kSmallThreads + tid;
+        if (i < n) {
+            bool bad;
+            const uint32_t k = leaf_key(xv[r], yv[r], d, L, bad);
+            key[i] = k;
+            atomicAdd(&h[k], 1);
+            mybad += bad ? 1 : 0;
+        }
+    }
+    if (mybad) atomicAdd(&nbad, mybad);
+    __syncthreads();
+    uint16_t* row = hist + int64_t(blockIdx.x) * bins;
+    for (int e = tid; e < bins; e += kSmallThreads) row[e] = uint16_t(h[e]);
+    if (tid == 0) bad_blk[blockIdx.x] = nbad;
+}
+
+// Leaf counts in LDS: 16 bits, kVec leaves a thread.
+constexpr int kSmallVec = 4;
+struct alignas(8) Counts {
+    uint16_t v[kSmallVec];
+};
+
+// Places of one tile's records, and the leaf ranges (the first workgroup).
+// Ranks as k_rscatter: wavefront w owns the input positions [256 w, 256 (w +
+// 1)) of the tile, 64 a round.  ONE (the only tile): the keys are computed
+// here, and the records are sorted in LDS and written out; else only the
+// permutation is, and k_small_gather moves the records (scattered eight-byte
+// stores take a cycle of the CU each: five a record from these few workgroups
+// cost more than the whole sort).
+template <bool ONE>
+__global__ void __launch_bounds__(kSmallThreads)
+k_small_sort(int n, int nblk, const uint32_t* __restrict__ kin, const double* __restrict__ x,
+             const double* __restrict__ y, const double* __restrict__ g, const Inst* __restrict__ inst,
+             uint32_t* __restrict__ key, const uint16_t* __restrict__ hist, int32_t* __restrict__ bad_blk, Records out,
+             float4* __restrict__ pk, int32_t* __restrict__ leaf_start)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int L = inst[0].L, bits = 2 * L, bins = 1 << bits;                 // at least kSmallVec
+    int* gbase = reinterpret_cast<int*>(smem);                               // [bins] the tile's place in every leaf
+    uint16_t* whist = reinterpret_cast<uint16_t*>(gbase + bins);             // [kSmallWaves][bins]
+    __shared__ int wsum[kSmallWaves];
+    __shared__ int nbad;
+    const int tid = threadIdx.x, lane = int(__lane_id()), w = tid >> 6, blk = int(blockIdx.x);
+    const Domain dm = inst[0].dom;
+    const int base = blk * kRadixTile;
+    const int first = base + w * (kRadixTile / kSmallWaves) + lane;          // the thread's records: first + 64 r
+    if (ONE && tid == 0) nbad = 0;
+
+    uint32_t kr[kSmallPer];
+    double xr[kSmallPer], yr[kSmallPer], gr[kSmallPer];
+    int mybad = 0;
+#pragma unroll
+    for (int r = 0; r < kSmallPer; ++r) {
+        const int ic = min(first + 64 * r, n - 1);
+        if constexpr (ONE) {
+            xr[r] = x[ic];
+            yr[r] = y[ic];
+            gr[r] = g ? g[ic] : 0.0;
+        } else {
+            kr[r] = kin[ic];
+        }
+    }
+    // this tile's part of every leaf: the counts of the tiles before it and of
+    // all tiles, kSmallVec leaves a thread (at most 4096 leaves)
+    const int d0 = tid * kSmallVec;
+    const bool mine = d0 < bins;
+    int pre[kSmallVec] = {0, 0, 0, 0}, tot[kSmallVec] = {0, 0, 0, 0};
+    if constexpr (!ONE) {
+        if (mine) {
+            const Counts* row = reinterpret_cast<const Counts*>(hist + d0);
+            const int stride = bins / kSmallVec;
+#pragma unroll 8
+            for (int b = 0; b < nblk; ++b) {
+                const Counts c = row[int64_t(b) * stride];
+#pragma unroll
+                for (int q = 0; q < kSmallVec; ++q) {
+                    tot[q] += c.v[q];
+                    pre[q] += b < blk ? c.v[q] : 0;
+                }
+            }
+        }
+    }
+    Counts* wz = reinterpret_cast<Counts*>(whist);
+    for (int e = tid; e < kSmallWaves * bins / kSmallVec; e += kSmallThreads) wz[e] = Counts{{0, 0, 0, 0}};
+    if constexpr (ONE) {
+#pragma unroll
+        for (int r = 0; r < kSmallPer; ++r) {
+            bool bad;
+            kr[r] = leaf_key(xr[r], yr[r], dm, L, bad);
+            if (first + 64 * r < n) {
+                key[first + 64 * r] = kr[r];
+                mybad += bad ? 1 : 0;
+            }
+        }
+    }
+    __syncthreads();
+
+    const uint64_t lt_mask = (uint64_t(1) << lane) - 1;
+    int lpos[kSmallPer];
+    uint16_t* wh = whist + w * bins;
+#pragma unroll
+    for (int r = 0; r < kSmallPer; ++r) {
+        const bool valid = first + 64 * r < n;
+        const uint32_t d = kr[r];
+        uint64_t same = __ballot(valid);
+        for (int b = 0; b < bits; ++b) {
+            const bool bit = (d >> b) & 1;
+            const uint64_t bb = __ballot(bit);
+            same &= bit ? bb : ~bb;
+        }
+        const int rank = __popcll(same & lt_mask);
+        const int before = wh[d];
+        __builtin_amdgcn_wave_barrier();
+        if (valid && rank == 0) wh[d] = uint16_t(before + __popcll(same));
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        lpos[r] = valid ? before + rank : -1;
+    }
+    if (ONE && mybad) atomicAdd(&nbad, mybad);
+    __syncthreads();
+
+    // the wavefronts' counts to their places within the tile's part of a leaf
+    int s = 0;
+    if (mine) {
+        int acc[kSmallVec] = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < kSmallWaves; ++k) {
+            Counts* c = reinterpret_cast<Counts*>(whist + k * bins + d0);
+            const Counts t = *c;
+            Counts o;
+#pragma unroll
+            for (int q = 0; q < kSmallVec; ++q) {
+                o.v[q] = uint16_t(acc[q]);
+                acc[q] += t.v[q];
+            }
+            *c = o;
+        }
+#pragma unroll
+        for (int q = 0; q < kSmallVec; ++q) {
+            if constexpr (ONE) tot[q] = acc[q];
+            s += tot[q];
+        }
+    }
+    const int inc = wave_incl_scan(s);
+    if (lane == 63) wsum[w] = inc;
+    __syncthreads();
+    int start = inc - s;
+#pragma unroll
+    for (int k = 0; k < kSmallWaves; ++k) start += k < w ? wsum[k] : 0;
+    if (mine) {
+#pragma unroll
+        for (int q = 0; q < kSmallVec; ++q) {
+            gbase[d0 + q] = start + pre[q];
+            if (blk == 0) leaf_start[d0 + q] = start;
+            start += tot[q];
+        }
+        if (blk == 0 && d0 + kSmallVec == bins) leaf_start[bins] = start;
+    }
+    if (ONE && tid == 0) bad_blk[0] = nbad;
+    __syncthreads();
+
+#pragma unroll
+    for (int r = 0; r < kSmallPer; ++r) {
+        if (lpos[r] < 0) continue;
+        lpos[r] += gbase[kr[r]] + wh[kr[r]];
+        if constexpr (!ONE) out.idx[lpos[r]] = uint32_t(first + 64 * r);
+    }
+    if constexpr (!ONE) return;
+    __syncthreads();
+    // the sorted tile in LDS, over the counts
+    double* sx = reinterpret_cast<double*>(smem);
+    double* sy = sx + kRadixTile;
+    double* sg = sy + kRadixTile;
+    uint32_t* sk = reinterpret_cast<uint32_t*>(sg + kRadixTile);
+    uint32_t* si = sk + kRadixTile;
+#pragma unroll
+    for (int r = 0; r < kSmallPer; ++r) {
+        if (lpos[r] < 0) continue;
+        sx[lpos[r]] = xr[r];
+        sy[lpos[r]] = yr[r];
+        sg[lpos[r]] = gr[r];
+        sk[lpos[r]] = kr[r];
+        si[lpos[r]] = uint32_t(first + 64 * r);
+    }
+    __syncthreads();
+    for (int j = tid; j < n; j += kSmallThreads) {
+        const uint32_t k = sk[j];
+        out.k[j] = k;
+        out.idx[j] = si[j];
+        out.x[j] = sx[j];
+        out.y[j] = sy[j];
+        if (out.g) out.g[j] = sg[j];
+        if (pk) pk[j] = leaf_record(k, sx[j], sy[j], sg[j], dm, L);
+    }
+}
+
+// The records of a small sort to their places.
+__global__ void __launch_bounds__(256)
+k_small_gather(int n, const uint32_t* __restrict__ perm, const uint32_t* __restrict__ key, const double* __restrict__ x,
+               const double* __restrict__ y, const double* __restrict__ g, const Inst* __restrict__ inst, Records out,
+               float4* __restrict__ pk)
+{
+    const int j = int(blockIdx.x) * 256 + int(threadIdx.x);
+    if (j >= n) return;
+    const uint32_t i = perm[j], k = key[i];
+    const double xv = x[i], yv = y[i], gv = g ? g[i] : 0.0;
+    out.k[j] = k;
+    out.x[j] = xv;
+    out.y[j] = yv;
+    if (out.g) out.g[j] = gv;
+    if (pk) pk[j] = leaf_record(k, xv, yv, gv, inst[0].dom, inst[0].L);
+}
+
 // Depth 0: one leaf, nothing to sort.
 __global__ void __launch_bounds__(256)
 k_copy_one_leaf(int n, const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ g,
@@ -616,6 +883,19 @@ int radix_passes(int key_bits) { return (key_bits + 7) / 8; }
 
 int64_t radix_blocks(int64_t n) { return (n + kRadixTile - 1) / kRadixTile; }
 
+bool small_sort(int64_t n_cap, int n_inst, int key_bits)
+{
+    return n_inst == 1 && key_bits >= 1 && key_bits <= kSmallKeyBits && radix_blocks(n_cap) <= kSmallTiles;
+}
+
+size_t hist_bytes(int64_t n_cap, int n_inst, int key_bits)
+{
+    const size_t nblk = size_t(radix_blocks(n_cap));
+    const size_t passes = sizeof(int32_t) * kRadixBins * nblk;
+    const size_t small = small_sort(n_cap, n_inst, key_bits) ? (sizeof(uint16_t) << key_bits) * nblk : 0;
+    return passes > small ? passes : small;
+}
+
 namespace {
 
 // Radix passes of at most this many tiles use the 1024-thread kernels.
@@ -624,12 +904,10 @@ namespace {
 #endif
 constexpr int kWideTilesMax = 2048;
 
-// Exclusive scan of hist[0..m) into out[0..m], out[m] = total.
-void scan_table(const Buffers& b, int64_t m, hipStream_t st)
+void scan_table(const Buffers& b, int nblk, hipStream_t st)
 {
-    const int nsb = int((m + kScanChunk - 1) / kScanChunk);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nsb), dim3(256), 0, st, m, b.hist, b.scan_part);
-    hipLaunchKernelGGL(k_scan_down, dim3(nsb), dim3(256), 0, st, m, nsb, b.hist, b.scan_part, b.hist_scan);
+    hipLaunchKernelGGL(k_scan_rows, dim3(kRadixBins), dim3(kRowScanThreads), 0, st, nblk, b.hist, b.hist_scan,
+                       b.scan_part);
 }
 
 }  // namespace
@@ -643,7 +921,25 @@ void sort_points(const Buffers& b, int n, const double* x, const double* y, cons
                  int64_t leaf_entries, hipStream_t st, const int32_t* n_dev = nullptr)
 {
     const int nblk = int(radix_blocks(n));
-    const int64_t m = int64_t(kRadixBins) * nblk;
+    if (b.small_sort) {
+        // 16-bit counts of the wavefronts and a place per leaf in LDS, then (one tile) its records
+        const size_t bins = size_t(1) << key_bits;
+        const size_t counts_lds = bins * (sizeof(int) + kSmallWaves * sizeof(uint16_t));
+        uint16_t* counts = reinterpret_cast<uint16_t*>(b.hist);
+        if (nblk == 1) {
+            const size_t lds = std::max(counts_lds, size_t(kRadixTile) * (3 * sizeof(double) + 2 * sizeof(uint32_t)));
+            hipLaunchKernelGGL(k_small_sort<true>, dim3(1), dim3(kSmallThreads), lds, st, n, nblk, nullptr, x, y, g,
+                               b.inst, key, counts, bad_blk, fin, pk, leaf_start);
+        } else {
+            hipLaunchKernelGGL(k_small_keys, dim3(nblk), dim3(kSmallThreads), bins * sizeof(int), st, n, x, y, b.inst,
+                               key, counts, bad_blk);
+            hipLaunchKernelGGL(k_small_sort<false>, dim3(nblk), dim3(kSmallThreads), counts_lds, st, n, nblk, key, x, y,
+                               g, b.inst, key, counts, bad_blk, fin, pk, leaf_start);
+            hipLaunchKernelGGL(k_small_gather, dim3(blocks_for(n, 256)), dim3(256), 0, st, n, fin.idx, key, x, y, g,
+                               b.inst, fin, pk);
+        }
+        return;
+    }
     const Records tmp{b.ktmp, b.itmp, b.xt, b.yt, g ? b.gt : nullptr};
     const bool wide = FMM_TREE_TPB == 1024 || (FMM_TREE_TPB == 0 && nblk <= kWideTilesMax);
     if (wide)
@@ -667,15 +963,15 @@ void sort_points(const Buffers& b, int n, const double* x, const double* y, cons
                 hipLaunchKernelGGL(k_rhist<1024>, dim3(nblk), dim3(1024), 0, st, n, kin, shift, nblk, b.hist, n_dev);
             else if (pass > 0)
                 hipLaunchKernelGGL(k_rhist<256>, dim3(nblk), dim3(256), 0, st, n, kin, shift, nblk, b.hist, n_dev);
-            scan_table(b, m, st);
+            scan_table(b, nblk, st);
             const bool last = pass == npass - 1;
             if (wide)
                 hipLaunchKernelGGL(k_rscatter<1024>, dim3(nblk), dim3(1024), 0, st, n, kin, iin, xin, yin, gin,
-                                   shift, nblk, b.hist, b.hist_scan, out, last ? pk : nullptr, b.inst, b.key_shift,
+                                   shift, nblk, b.hist, b.hist_scan, b.scan_part, out, last ? pk : nullptr, b.inst, b.key_shift,
                                    n_dev);
             else
                 hipLaunchKernelGGL(k_rscatter<256>, dim3(nblk), dim3(256), 0, st, n, kin, iin, xin, yin, gin,
-                                   shift, nblk, b.hist, b.hist_scan, out, last ? pk : nullptr, b.inst, b.key_shift,
+                                   shift, nblk, b.hist, b.hist_scan, b.scan_part, out, last ? pk : nullptr, b.inst, b.key_shift,
                                    n_dev);
             kin = out.k;
             iin = out.idx;
@@ -714,7 +1010,6 @@ hipError_t launch_sort_keys(const Buffers& b, int n, const uint32_t* key, const 
     const int npass = radix_passes(key_bits);
     if (n <= 0 || npass <= 0) return hipErrorInvalidValue;
     const int nblk = int(radix_blocks(n));
-    const int64_t m = int64_t(kRadixBins) * nblk;
     const Records fin{ks, perm, xs, ys, gs};
     const Records tmp{b.ktmp, b.itmp, b.xt, b.yt, b.gt};
     const bool wide = nblk <= kWideTilesMax;
@@ -728,13 +1023,13 @@ hipError_t launch_sort_keys(const Buffers& b, int n, const uint32_t* key, const 
             hipLaunchKernelGGL(k_rhist<1024>, dim3(nblk), dim3(1024), 0, st, n, kin, shift, nblk, b.hist, nullptr);
         else
             hipLaunchKernelGGL(k_rhist<256>, dim3(nblk), dim3(256), 0, st, n, kin, shift, nblk, b.hist, nullptr);
-        scan_table(b, m, st);
+        scan_table(b, nblk, st);
         if (wide)
             hipLaunchKernelGGL(k_rscatter<1024>, dim3(nblk), dim3(1024), 0, st, n, kin, iin, xin, yin, gin, shift,
-                               nblk, b.hist, b.hist_scan, out, nullptr, nullptr, 0, nullptr);
+                               nblk, b.hist, b.hist_scan, b.scan_part, out, nullptr, nullptr, 0, nullptr);
         else
             hipLaunchKernelGGL(k_rscatter<256>, dim3(nblk), dim3(256), 0, st, n, kin, iin, xin, yin, gin, shift,
-                               nblk, b.hist, b.hist_scan, out, nullptr, nullptr, 0, nullptr);
+                               nblk, b.hist, b.hist_scan, b.scan_part, out, nullptr, nullptr, 0, nullptr);
         kin = out.k;
         iin = out.idx;
         xin = out.x;
