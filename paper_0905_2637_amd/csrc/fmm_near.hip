@@ -302,6 +302,8 @@ __device__ __forceinline__ void leaf_near_far(const LeafCtx& c, int lane, void* 
         for (int k = lane; k < P; k += 64) le_sh[k] = le_leaf[int64_t(c.m) * P + k];
 
     for (int c0 = 0; c0 < c.nt; c0 += T) {
+        // targets per lane that any lane of the chunk has
+        const int rows = 1 + (c.nt - c0 > TG) + (c.nt - c0 > 2 * TG) + (c.nt - c0 > 3 * TG);
         double xi[R], yi[R], ax[R], ay[R];
         float oxi[R], oyi[R], fx[R], fy[R];
 #pragma unroll
@@ -331,8 +333,24 @@ __device__ __forceinline__ void leaf_near_far(const LeafCtx& c, int lane, void* 
             if constexpr (MIXED) { px = tx[c.s0 + il]; py = ty[c.s0 + il]; }
         }
 
+        // Lennard-Jones: the staged sources beyond the cutoff of the leaf are
+        // left out (their terms are zero; leaves of 16, cutoff 0.56 leaf
+        // widths: about half of them, 157 -> 133 us).  Targets clamped into the leaf from
+        // outside the square lie outside it: then all are kept.
+        bool cull = false;
+        double half = 0.0;
+        if constexpr (KER == kNearLJ) {
+            const double h = 0.5 / c.s;
+            bool in = true;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                in = in && fabs(xi[r] - c.cx) <= h * (1.0 + 1e-7) && fabs(yi[r] - c.cy) <= h * (1.0 + 1e-7);
+            cull = __ballot(!in) == 0;
+            half = h * (1.0 + 1e-6);
+        }
+
         for (int base = 0; base < tot; base += chunk) {
-            const int cnt = min(chunk, tot - base);
+            int cnt = min(chunk, tot - base);
             // every lane finds the neighbour leaf of each of its slots, then all
             // loads are issued before the first wait (one memory round trip)
             Stage val[kStageSlots];
@@ -366,14 +384,38 @@ __device__ __forceinline__ void leaf_near_far(const LeafCtx& c, int lane, void* 
                 }
             }
             wave_sync();
+            if constexpr (KER == kNearLJ) {
+                // kept sources side by side, then inert ones up to a multiple of S
+                int kept = 0;
 #pragma unroll
-            for (int sl = 0; sl < kStageSlots; ++sl) {
-                const int k = lane + 64 * sl;
-                src[k] = val[sl];   // inert past cnt: a slice's last step reads them
+                for (int sl = 0; sl < kStageSlots; ++sl) {
+                    const double ex = fmax(fabs(val[sl].x - c.cx) - half, 0.0);
+                    const double ey = fmax(fabs(val[sl].y - c.cy) - half, 0.0);
+                    const bool keep = lane + 64 * sl < cnt && (!cull || fma(ex, ex, ey * ey) <= c.k.rc2 * (1.0 + 1e-9));
+                    const uint64_t m = __ballot(keep);
+                    if (keep) src[kept + __popcll(m & ((uint64_t(1) << lane) - 1))] = val[sl];
+                    kept += __popcll(m);
+                }
+                cnt = kept;
+                if (lane < S && kept + lane < kNearStage) src[kept + lane] = Src64{1.0e10, 1.0e10, 0.0};
+            } else {
+#pragma unroll
+                for (int sl = 0; sl < kStageSlots; ++sl) {
+                    const int k = lane + 64 * sl;
+                    src[k] = val[sl];   // inert past cnt: a slice's last step reads them
+                }
             }
             wave_sync();
-            if constexpr (MIXED) p2p_f32<R, KER>(src, cnt, S, si, c.c2, oxi, oyi, fx, fy);
-            else p2p_f64<R, KER>(src, cnt, S, si, c.k, xi, yi, ax, ay);
+            if constexpr (MIXED) {
+                // the same sums without the rows that hold no target (a chunk
+                // of 33 to 48 has three of four): a target's sum does not
+                // depend on how many share its lane
+                if (R == 4 && rows == 3) p2p_f32<3, KER>(src, cnt, S, si, c.c2, oxi, oyi, fx, fy);
+                else if (R == 4 && rows <= 2) p2p_f32<2, KER>(src, cnt, S, si, c.c2, oxi, oyi, fx, fy);
+                else p2p_f32<R, KER>(src, cnt, S, si, c.c2, oxi, oyi, fx, fy);
+            } else {
+                p2p_f64<R, KER>(src, cnt, S, si, c.k, xi, yi, ax, ay);
+            }
         }
 
         // combine the S slices through the staging area: every slice lane
@@ -594,9 +636,13 @@ __device__ __forceinline__ void quad_pairs(const Src64* qsh, int lane, int w, co
 }
 
 // WAVES wavefronts per workgroup, one leaf each (four: one quad); the work
-// table gives every instance ceil(4^L / WAVES) workgroups.
+// table gives every instance ceil(4^L / WAVES) workgroups.  The occupancy is
+// set where the compiler would spend registers past it: mixed 83 instead of 66
+// (2^22 clustered particles 1,341 -> 1,250 us, with the row variants of
+// leaf_near_far; 512 instances of 64 per leaf 2,782 -> 2,390 us), and
+// Lennard-Jones 105 (144 -> 133 us with five wavefronts per SIMD).
 template <int P, bool MIXED, int WAVES, int KER>
-__global__ void __launch_bounds__(64 * WAVES)
+__global__ void __launch_bounds__(64 * WAVES, MIXED ? 7 : KER == kNearLJ ? 5 : 0)
 k_p2p_l2p(Work wk, int n_inst, const Inst* __restrict__ inst, const int32_t* __restrict__ leaf_start_all,
           const double* __restrict__ xs, const double* __restrict__ ys, const double* __restrict__ gs,
           const float4* __restrict__ pk, const uint32_t* __restrict__ perm, const cd* __restrict__ le_all,
