@@ -251,7 +251,7 @@ Layout make_layout(const Shape& sh, int P, bool mixed)
     ly.le_part[1] = take(sizeof(cd) * size_t(sh.split_boxes) * P);
     ly.t_m2m = take(sizeof(cd) * 4 * P * P);
     ly.t_l2l = take(sizeof(cd) * 4 * P * P);
-    ly.t_h64 = take(sizeof(cd) * kHankelGrid * kHankelGrid * (2 * P - 1));
+    ly.t_h64 = take(sizeof(cd) * kHankelGrid * kHankelGrid * hankel_row(P));
     ly.t_h32 = take(sizeof(cf) * kHankelGrid * kHankelGrid * (2 * P - 1));
     ly.t_sin = take(sizeof(double) * P);
     ly.t_sout = take(sizeof(double) * P);
@@ -693,7 +693,8 @@ fmm_status make_plan(const fmm_params* prm, Shape&& sh, bool batch, void* d_work
     b.fgt_h = fgt ? reinterpret_cast<double*>(base + ly.fgt_h) : nullptr;
 
     const size_t nh = size_t(kHankelGrid) * kHankelGrid * (2 * P - 1);
-    std::vector<cd> m2m(size_t(4) * P * P), l2l(size_t(4) * P * P), h64(nh);
+    std::vector<cd> m2m(size_t(4) * P * P), l2l(size_t(4) * P * P);
+    std::vector<cd> h64(size_t(kHankelGrid) * kHankelGrid * hankel_row(P));
     std::vector<cf> h32(nh);
     std::vector<double> sin_(P), sout_(P);
     build_tables(P, prm->p, m2m.data(), l2l.data(), h64.data(), h32.data(), sin_.data(), sout_.data());

@@ -15,10 +15,10 @@
 // the scalar/L1 caches.  The multipole arrays already hold abar (the upward
 // sweep stores them that way), so only the output scaling 1/l! remains.  The
 // product is dense: every (k, l) pair is one complex multiply-add, 8 p^2
-// flops per interaction-list pair; on the vector units (FP64, and FP32 in
-// the mixed form) the members are taken two at a time where the square's
-// symmetries relate their data, which halves that (see the work items
-// below).
+// flops per interaction-list pair; on the vector units the members whose data
+// the square's symmetries relate are taken together: two at a time for the
+// FP32 levels of the mixed form (half the flops), up to eight at a time in
+// FP64 (a fifth).  See the work items and classes below.
 //
 // Lane mapping: a workgroup of 4 wavefronts covers 16 x 16 target boxes of
 // one level; wavefront c holds the 64 boxes in child position c of their
@@ -230,6 +230,254 @@ __device__ __forceinline__ void m2l_items_block(T* bx, T* by, const cplx<T>* __r
     m2l_kind_block<T, P, kItemOneDiag, K0>(bx, by, H, cx, cy, g, G, 14, 15, zero_slot, slot, term);
 }
 
+// FP64 M2L by the whole symmetry group of the square.  Beside conjugation and
+// negation, reflection in a diagonal relates the data: with s = +-1,
+//   h_n(s i conj tau) = (-s i)^(n+1) conj h_n(tau),
+// real factors or a swap of the parts, by n mod 4.  So the up to eight offsets
+// (+-a, +-b), (+-b, +-a) share the data h_n = u + i v of tau = (a, b): with
+// members A, B, C, D at tau, conj tau, -conj tau, -tau and E, F, G, H at the
+// same of s i conj tau, sigma = (-1)^(n+1) and
+//   P = (A + B) + sigma (C + D),   Q = (A - B) - sigma (C - D),   P', Q' alike,
+// their contribution is u X + v Y, for n mod 4 =
+//   0: X = P - s i Q', Y = i Q - s P'     1: X = P - P', Y = i (Q + Q')
+//   2: X = P + s i Q', Y = i Q + s P'     3: X = P + P', Y = i (Q - Q').
+// The 27 members of child (0, 0) are seven classes: (1, 2) with eight members,
+// (3, 1) and (3, 2) with four (3 occurs with one sign only), (2, 0) with four
+// and (3, 0) with two, whose data are real (v = 0), and the diagonal (2, 2)
+// with four and (3, 3) with one, which a diagonal reflection maps to
+// themselves: real for n = 3, imaginary for n = 1 mod 4 and of equal parts
+// else (v = s u for n = 2 mod 4, -s u for n = 0), so that u X + v Y is one
+// product there too.  The other children mirror the offsets (x for child x =
+// 1, y for y = 1; s is the product of the mirrors' signs).  20 multiply-adds
+// per output and input term and 144 additions per input term, against 52 and
+// 48 for the pairs above.  The FP32 levels keep the pairs: their sums would
+// round differently.  So does FP64 past P = 24: the operands of a class and
+// 2 P accumulators do not fit the registers (248 us by pairs, 490 by classes
+// at P = 32, 1M particles).  M2L stage, pairs -> classes: 32 -> 29 us (P = 8),
+// 50 -> 43 (12), 86.5 -> 72 (17), 103 -> 78 (20), 139 -> 119 (24) at 1M
+// particles, depth 8; 1175 -> 778 at 16M, depth 10, P = 20; 39 -> 30 at 200k,
+// depth 6, P = 17.  Bound by FP64 issue at two wavefronts per SIMD; one input
+// term at a time (three wavefronts fit) reads each datum twice as often for
+// its product: 81 us at P = 17, 267 at 24.  Data residue by residue instead
+// of in order of n (below): 74 -> 72 at P = 17, 134 -> 119 at 24, 824 -> 778
+// at 16M.
+constexpr int kHalo = 20;             // a workgroup's 16 x 16 targets draw on the 20 x 20 boxes around them
+constexpr int kM2LClassK = 2;         // input terms a class takes at a time
+enum : int { kC12 = 1, kC31 = 2, kC32 = 4, kC22 = 8, kC33 = 16, kC20 = 32, kC30 = 64 };
+// classes of workgroup row g of G, of about equal work
+__device__ __forceinline__ int m2l_class_mask(int g, int G)
+{
+    if (G == 1) return 127;
+    if (G == 2) return g == 0 ? kC12 | kC31 | kC33 : kC32 | kC22 | kC20 | kC30;
+    return g == 0 ? kC12 | kC22 : g == 1 ? kC31 | kC20 : kC32 | kC30 | kC33;
+}
+
+__device__ __forceinline__ cd operator+(cd a, cd b) { return cd{a.x + b.x, a.y + b.y}; }
+__device__ __forceinline__ cd operator-(cd a, cd b) { return cd{a.x - b.x, a.y - b.y}; }
+// a + c b and a + c i b for a real c
+__device__ __forceinline__ cd add_scaled(cd a, double c, cd b) { return cd{fma(c, b.x, a.x), fma(c, b.y, a.y)}; }
+__device__ __forceinline__ cd add_scaled_i(cd a, double c, cd b) { return cd{fma(-c, b.y, a.x), fma(c, b.x, a.y)}; }
+__device__ __forceinline__ cd times_i(cd a) { return cd{-a.y, a.x}; }
+
+// Data of the terms n = RES mod 4 that input terms K0 .. K0 + K - 1 meet
+// (n < 2P - 1), from a row stored residue by residue (hankel_slot).
+template <int P, int K0, int K, int RES>
+struct M2LData {
+    static constexpr int kFirst = (K0 - RES + 3) / 4;                                 // n = 4 i + RES >= K0
+    static constexpr int kLast = (K0 + K + P - 2 < 2 * P - 2 ? K0 + K + P - 2 : 2 * P - 2) - RES;
+    static constexpr int kCount = kLast < 0 ? 0 : kLast / 4 - kFirst + 1;
+    cplx<double> h[kCount > 0 ? kCount : 1];
+    __device__ __forceinline__ void load(const cplx<double>* __restrict__ row)
+    {
+#pragma unroll
+        for (int i = 0; i < kCount; ++i) h[i] = row[hankel_slot(P, 4 * (kFirst + i) + RES)];
+    }
+};
+
+// b += u_n X + v_n Y over those n.  V: 0 no Y (real data, or folded into X), 1
+// both, 2 only Y
+template <int P, int K0, int K, int RES, int V>
+__device__ __forceinline__ void m2l_residue(double* bx, double* by, const M2LData<P, K0, K, RES>& d, const cd (&X)[K],
+                                            const cd (&Y)[K])
+{
+    using D = M2LData<P, K0, K, RES>;
+#pragma unroll
+    for (int i = 0; i < D::kCount; ++i) {
+        const double u = d.h[i].x, v = d.h[i].y;
+#pragma unroll
+        for (int kk = 0; kk < K; ++kk) {
+            const int j = 4 * (D::kFirst + i) + RES - K0 - kk;
+            if (K0 + kk >= P || j < 0 || j >= P) continue;
+            if (V != 2) {
+                bx[j] = fma(u, X[kk].x, bx[j]);
+                by[j] = fma(u, X[kk].y, by[j]);
+            }
+            if (V != 0) {
+                bx[j] = fma(v, Y[kk].x, bx[j]);
+                by[j] = fma(v, Y[kk].y, by[j]);
+            }
+        }
+    }
+}
+
+// One class: sources() reads and combines its members, form<n mod 4>(X, Y)
+// forms that residue's operands.  V1 .. V2: m2l_residue's V for n = 1, 3, 0, 2
+// mod 4.  The data of a residue are loaded (scalar loads) while the one before
+// multiplies; the barriers keep the scheduler from forming several residues'
+// operands at once, which spills.
+template <int P, int K0, int K, int V1, int V3, int V0, int V2, typename Sources, typename Form>
+__device__ __forceinline__ void m2l_class(double* bx, double* by, const cplx<double>* __restrict__ row, Sources sources,
+                                          Form form)
+{
+    M2LData<P, K0, K, 1> d1;
+    M2LData<P, K0, K, 3> d3;
+    M2LData<P, K0, K, 0> d0;
+    M2LData<P, K0, K, 2> d2;
+    cd X[K], Y[K];
+    d1.load(row);
+    sources();
+    form(std::integral_constant<int, 1>{}, X, Y);
+    d3.load(row);
+    __builtin_amdgcn_sched_barrier(0);
+    m2l_residue<P, K0, K, 1, V1>(bx, by, d1, X, Y);
+    __builtin_amdgcn_sched_barrier(0);
+    form(std::integral_constant<int, 3>{}, X, Y);
+    d0.load(row);
+    __builtin_amdgcn_sched_barrier(0);
+    m2l_residue<P, K0, K, 3, V3>(bx, by, d3, X, Y);
+    __builtin_amdgcn_sched_barrier(0);
+    form(std::integral_constant<int, 0>{}, X, Y);
+    d2.load(row);
+    __builtin_amdgcn_sched_barrier(0);
+    m2l_residue<P, K0, K, 0, V0>(bx, by, d0, X, Y);
+    __builtin_amdgcn_sched_barrier(0);
+    form(std::integral_constant<int, 2>{}, X, Y);
+    __builtin_amdgcn_sched_barrier(0);
+    m2l_residue<P, K0, K, 2, V2>(bx, by, d2, X, Y);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Input terms K0 .. K0 + K - 1 of the classes in `mask` for child (cx, cy):
+// the box at offset (dx, dy) from the target's halo slot `mine` is slot mine +
+// dy kHalo + dx, term(slot, k) reads its term k.
+template <int P, int K0, int K, typename Term>
+__device__ __forceinline__ void m2l_classes(double* bx, double* by, const cplx<double>* __restrict__ H, int cx, int cy,
+                                            int mask, int mine, Term term)
+{
+    const int sx = cx ? -1 : 1, sy = cy ? -1 : 1;
+    const double s = double(sx * sy);
+    const auto data = [&](int a, int b) { return H + ((sy * b + 3) * kHankelGrid + (sx * a + 3)) * hankel_row(P); };
+    // the 27 addresses are formed again for every block: kept, they would take
+    // 27 registers
+    asm volatile("" : "+v"(mine));
+    const auto load = [&](int dx, int dy, cd (&r)[K]) {
+        const int sl = mine + (sy * dy * kHalo + sx * dx);
+#pragma unroll
+        for (int kk = 0; kk < K; ++kk) r[kk] = K0 + kk < P ? term(sl, K0 + kk) : cd{0.0, 0.0};
+    };
+    // P and Q of sigma = 1 (p, q) and -1 (r, t); the primed ones likewise
+    cd p[K], q[K], r[K], t[K], p1[K], q1[K], r1[K], t1[K];
+    const auto four = [&](int a, int b, cd (&pp)[K], cd (&qq)[K], cd (&rr)[K], cd (&tt)[K]) {
+        load(a, b, pp);
+        load(a, -b, qq);
+        load(-a, b, rr);
+        load(-a, -b, tt);
+#pragma unroll
+        for (int kk = 0; kk < K; ++kk) {
+            const cd s1 = pp[kk] + qq[kk], d1 = pp[kk] - qq[kk], s2 = rr[kk] + tt[kk], d2 = rr[kk] - tt[kk];
+            pp[kk] = s1 + s2;
+            qq[kk] = d1 - d2;
+            rr[kk] = s1 - s2;
+            tt[kk] = d1 + d2;
+        }
+    };
+    const auto two = [&](int ax, int ay, int bx2, int by2, cd (&sum)[K], cd (&diff)[K]) {
+        load(ax, ay, sum);
+        load(bx2, by2, diff);
+#pragma unroll
+        for (int kk = 0; kk < K; ++kk) {
+            const cd a = sum[kk], b = diff[kk];
+            sum[kk] = a + b;
+            diff[kk] = a - b;
+        }
+    };
+    if (mask & kC12)
+        m2l_class<P, K0, K, 1, 1, 1, 1>(bx, by, data(1, 2), [&] {
+            four(1, 2, p, q, r, t);
+            four(2, 1, p1, q1, r1, t1);
+        }, [&](auto res, cd (&X)[K], cd (&Y)[K]) {
+            constexpr int R = decltype(res)::value;
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) {
+                if constexpr (R == 1) X[kk] = p[kk] - p1[kk], Y[kk] = times_i(q[kk] + q1[kk]);
+                if constexpr (R == 3) X[kk] = p[kk] + p1[kk], Y[kk] = times_i(q[kk] - q1[kk]);
+                if constexpr (R == 0) X[kk] = add_scaled_i(r[kk], -s, t1[kk]), Y[kk] = add_scaled(times_i(t[kk]), -s, r1[kk]);
+                if constexpr (R == 2) X[kk] = add_scaled_i(r[kk], s, t1[kk]), Y[kk] = add_scaled(times_i(t[kk]), s, r1[kk]);
+            }
+        });
+    // (3, b): members A, B, E, G; the primed P and Q of sigma = -1 are those of sigma = 1 exchanged
+    for (int b = 1; b <= 2; ++b)
+        if (mask & (b == 1 ? kC31 : kC32))
+            m2l_class<P, K0, K, 1, 1, 1, 1>(bx, by, data(3, b), [&] {
+                two(3, b, 3, -b, p, q);
+                two(b, 3, -b, 3, p1, q1);
+            }, [&](auto res, cd (&X)[K], cd (&Y)[K]) {
+                constexpr int R = decltype(res)::value;
+#pragma unroll
+                for (int kk = 0; kk < K; ++kk) {
+                    if constexpr (R == 1) X[kk] = p[kk] - p1[kk], Y[kk] = times_i(q[kk] + q1[kk]);
+                    if constexpr (R == 3) X[kk] = p[kk] + p1[kk], Y[kk] = times_i(q[kk] - q1[kk]);
+                    if constexpr (R == 0) X[kk] = add_scaled_i(p[kk], -s, p1[kk]), Y[kk] = add_scaled(times_i(q[kk]), -s, q1[kk]);
+                    if constexpr (R == 2) X[kk] = add_scaled_i(p[kk], s, p1[kk]), Y[kk] = add_scaled(times_i(q[kk]), s, q1[kk]);
+                }
+            });
+    // the diagonal: real (n = 3), imaginary (n = 1), equal parts (v = -s u for n = 0, s u for n = 2)
+    if (mask & kC22)
+        m2l_class<P, K0, K, 2, 0, 0, 0>(bx, by, data(2, 2), [&] { four(2, 2, p, q, r, t); },
+                                        [&](auto res, cd (&X)[K], cd (&Y)[K]) {
+            constexpr int R = decltype(res)::value;
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) {
+                if constexpr (R == 1) Y[kk] = times_i(q[kk]);
+                if constexpr (R == 3) X[kk] = p[kk];
+                if constexpr (R == 0) X[kk] = add_scaled_i(r[kk], -s, t[kk]);
+                if constexpr (R == 2) X[kk] = add_scaled_i(r[kk], s, t[kk]);
+            }
+        });
+    if (mask & kC33)
+        m2l_class<P, K0, K, 2, 0, 0, 0>(bx, by, data(3, 3), [&] { load(3, 3, p); }, [&](auto res, cd (&X)[K], cd (&Y)[K]) {
+            constexpr int R = decltype(res)::value;
+#pragma unroll
+            for (int kk = 0; kk < K; ++kk) {
+                if constexpr (R == 1) Y[kk] = times_i(p[kk]);
+                if constexpr (R == 3) X[kk] = p[kk];
+                if constexpr (R == 0) X[kk] = add_scaled_i(p[kk], -s, p[kk]);
+                if constexpr (R == 2) X[kk] = add_scaled_i(p[kk], s, p[kk]);
+            }
+        });
+    // the axes, real data: P = Q = A + sigma D, P' = Q' = E + sigma H
+    const auto axis = [&](auto res, cd (&X)[K], const cd (&po)[K], const cd (&pe)[K], const cd (&p1o)[K], const cd (&p1e)[K]) {
+        constexpr int R = decltype(res)::value;
+#pragma unroll
+        for (int kk = 0; kk < K; ++kk) {
+            if constexpr (R == 1) X[kk] = po[kk] - p1o[kk];
+            if constexpr (R == 3) X[kk] = po[kk] + p1o[kk];
+            if constexpr (R == 0) X[kk] = add_scaled_i(pe[kk], -s, p1e[kk]);
+            if constexpr (R == 2) X[kk] = add_scaled_i(pe[kk], s, p1e[kk]);
+        }
+    };
+    if (mask & kC20)
+        m2l_class<P, K0, K, 0, 0, 0, 0>(bx, by, data(2, 0), [&] {
+            two(2, 0, -2, 0, p, r);
+            two(0, 2, 0, -2, p1, r1);
+        }, [&](auto res, cd (&X)[K], cd (&)[K]) { axis(res, X, p, r, p1, r1); });
+    if (mask & kC30)
+        m2l_class<P, K0, K, 0, 0, 0, 0>(bx, by, data(3, 0), [&] {
+            load(3, 0, p);
+            load(0, 3, p1);
+        }, [&](auto res, cd (&X)[K], cd (&)[K]) { axis(res, X, p, p, p1, p1); });
+}
+
 // f(std::integral_constant<int, c>) for c = 0 .. sizeof...(C) - 1, in order.
 template <typename F, int... C>
 __device__ __forceinline__ void m2l_for_chunks(F f, std::integer_sequence<int, C...>)
@@ -247,13 +495,12 @@ struct M2LOut {
 // FP64 M2L with the sources of the workgroup's tile staged in LDS once: the
 // 16 x 16 target boxes of a workgroup (four child classes of an 8 x 8 parent
 // block) draw their interaction lists from the 20 x 20 boxes around them;
-// boxes outside the grid are staged as zeros.  Same work items and block
-// order as k_m2l_chunks, so the two give the same bits.  The stage takes
+// boxes outside the grid are staged as zeros.  Same classes and block order
+// as k_m2l_chunks, so the two give the same bits.  The stage takes
 // 6.4 KB per expansion term (109 KB at p = 17), which leaves room for one
 // workgroup per CU: on grids of a few tens of workgroups it is the faster
 // (the whole stage loaded once); on larger ones the chunked stage, whose
 // smaller footprint lets more wavefronts hide the loads.
-constexpr int kHalo = 20;
 constexpr int kM2LStageMaxWg = 32;
 template <int P>
 __global__ void __launch_bounds__(256)
@@ -304,12 +551,13 @@ k_m2l64_lds(Work wk, int n_inst, const Inst* __restrict__ inst, const cd* __rest
     double bx_[P], by_[P];
 #pragma unroll
     for (int k = 0; k < P; ++k) { bx_[k] = 0.0; by_[k] = 0.0; }
-    // the work items block by block, in the order of k_m2l_chunks
-    auto slot = [&](int dx, int dy) { return (tb + dy - y_lo) * kHalo + (ta + dx - x_lo); };
+    // the classes block by block, in the order of k_m2l_chunks
+    const int mine = (tb - y_lo) * kHalo + (ta - x_lo);
     auto term = [&](int sl, int k) { return sA[sl * P + k]; };
+    const int mask = m2l_class_mask(g, G);
     m2l_for_chunks([&](auto c) {
-        m2l_items_block<double, P, decltype(c)::value * kM2LK>(bx_, by_, H, cx, cy, g, G, kHalo * kHalo, slot, term);
-    }, std::make_integer_sequence<int, (P + kM2LK - 1) / kM2LK>{});
+        m2l_classes<P, decltype(c)::value * kM2LClassK, kM2LClassK>(bx_, by_, H, cx, cy, mask, mine, term);
+    }, std::make_integer_sequence<int, (P + kM2LClassK - 1) / kM2LClassK>{});
     if (active) {
         cd* dst = le + (level_offset(l) + int64_t(morton(uint32_t(ta), uint32_t(tb)))) * P;
 #pragma unroll
@@ -320,19 +568,19 @@ k_m2l64_lds(Work wk, int n_inst, const Inst* __restrict__ inst, const cd* __rest
     }
 }
 
-// M2L by symmetric pairs (T = double: every FP64 level but the smallest
-// launches; T = float: the FP32 levels of the mixed form on the vector
-// units) with the workgroup's sources staged in LDS kM2LK terms at a time:
+// M2L by symmetry classes (T = double: every FP64 level but the smallest
+// launches; P = 32 by pairs) and by symmetric pairs (T = float: the FP32 levels
+// of the mixed form on the vector units) with the workgroup's sources staged in LDS kM2LK terms at a time:
 // the 16 x 16 targets of a workgroup draw every source from the 20 x 20
 // boxes around them, so chunk c holds terms 4c .. 4c + 3 of those 400 boxes
 // (25.6 KB in FP64, k-major, zeros outside the level and past p, one zero
 // box at the end for the item without a partner) and every wavefront runs
-// block c of all its work items from it.  The loads of a chunk are
+// block c of all its work items or classes from it.  The loads of a chunk are
 // coalesced and shared by the workgroup's 256 targets instead of issued per
-// lane and member; in FP64 the same items and block order as k_m2l64_lds,
+// lane and member; in FP64 the same classes and block order as k_m2l64_lds,
 // so the two give the same bits.
 template <int P, typename T>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P > 24 ? 2 : 3)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(std::is_same<T, double>::value ? 2 : 3)))
 k_m2l_chunks(Work wk, int n_inst, const Inst* __restrict__ inst, const cd* __restrict__ me_all, M2LOut dst_,
              const cplx<T>* __restrict__ H, const double* __restrict__ sout_)
 {
@@ -394,8 +642,17 @@ k_m2l_chunks(Work wk, int n_inst, const Inst* __restrict__ inst, const cd* __res
         }
         if (threadIdx.x < kM2LK) sA[threadIdx.x][NBOX] = cplx<T>{T(0), T(0)};
         __syncthreads();
-        // block c of every work item of this row
-        m2l_items_block<T, P, k0>(bx_, by_, H, cx, cy, g, G, NBOX, slot, [&](int sl, int k) { return sA[k - k0][sl]; });
+        // block c of every work item (FP64: class) of this row
+        if constexpr (std::is_same<T, double>::value && hankel_by_residue(P)) {
+            const auto term = [&](int sl, int k) { return cd{sA[k - k0][sl].x, sA[k - k0][sl].y}; };
+            m2l_for_chunks([&](auto i) {
+                constexpr int kb = k0 + decltype(i)::value * kM2LClassK;
+                if constexpr (kb < P) m2l_classes<P, kb, kM2LClassK>(bx_, by_, H, cx, cy, m2l_class_mask(g, G), slot(0, 0), term);
+            }, std::make_integer_sequence<int, kM2LK / kM2LClassK>{});
+        } else {
+            m2l_items_block<T, P, k0>(bx_, by_, H, cx, cy, g, G, NBOX, slot,
+                                      [&](int sl, int k) { return sA[k - k0][sl]; });
+        }
     }, std::make_integer_sequence<int, NB>{});
     if (active) {
         cd* dst = le + (level_offset(l) + int64_t(morton(uint32_t(ta), uint32_t(tb)))) * P;

@@ -33,6 +33,15 @@ constexpr int kMaxDepth = 13;
 constexpr int kMaxP = 32;
 constexpr int kMaxPMixed = 22;      // FP32 translation data overflows beyond this
 constexpr int kHankelGrid = 7;      // integer M2L offsets (dx, dy) with |dx|, |dy| <= 3
+// A row of the FP64 translation data h_0 .. h_(2P-2): residue by residue of n
+// mod 4 for the M2L by symmetry classes (P <= 24; beyond, its operands do not
+// fit the registers), else in order.
+__host__ __device__ constexpr bool hankel_by_residue(int P) { return P <= 24; }
+__host__ __device__ constexpr int hankel_row(int P) { return hankel_by_residue(P) ? (2 * P + 2) / 4 * 4 : 2 * P - 1; }
+__host__ __device__ constexpr int hankel_slot(int P, int n)
+{
+    return hankel_by_residue(P) ? (n % 4) * (hankel_row(P) / 4) + n / 4 : n;
+}
 constexpr int kBBoxBlocks = 256;
 constexpr int kMaxInstances = 1 << 16;
 // Widest domain and narrowest Gaussian core: the FP64 near field takes four
@@ -177,7 +186,7 @@ struct Buffers {
     cd* le_part[2];        // [sum Lambda(split)_i * P] partial M2L sums of the split levels
     cd* t_m2m;             // [4][P][P]
     cd* t_l2l;             // [4][P][P]
-    cd* t_h64;             // [49][2P-1] M2L translation data, FP64
+    cd* t_h64;             // [49][hankel_row(P)] M2L translation data, FP64
     cf* t_h32;             // [49][2P-1] M2L translation data, FP32
     double* t_sin;         // [P] (-1)^(k+1) / k!
     double* t_sout;        // [P] 1 / l!
