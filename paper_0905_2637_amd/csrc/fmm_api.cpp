@@ -212,7 +212,7 @@ Layout make_layout(const Shape& sh, int P, bool mixed)
     const size_t n = size_t(std::max<int64_t>(sh.n_cap, 1));
     const size_t m = size_t(sh.m_cap);
     const size_t nm = std::max(n, m);   // the radix temporaries serve both point sets
-    const size_t nblk = size_t(radix_blocks(int64_t(nm)));
+    const size_t nblk = size_t(sort_tiles(int64_t(nm), sh.n_inst, seg_sort(sh.n_cap, sh.n_inst, 2 * sh.Lmax)));
     Layout ly{};
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes); return o; };
@@ -221,7 +221,7 @@ Layout make_layout(const Shape& sh, int P, bool mixed)
     ly.bad_blk = take(sizeof(int32_t) * nblk);
     ly.bbox = take(sizeof(double) * 8 * kBBoxBlocks);
     ly.leaf_start = take(sizeof(int32_t) * size_t(sh.leaf_entries));
-    ly.hist = take(hist_bytes(int64_t(nm), sh.batched ? 0 : sh.n_inst, sh.key_bits));
+    ly.hist = take(hist_bytes(int64_t(nm), sh.batched ? 0 : sh.n_inst, sh.key_bits, int64_t(nblk)));
     ly.hist_scan = take(sizeof(int32_t) * kHistDigits * nblk);
     ly.scan_part = take(sizeof(int32_t) * kHistDigits);
     ly.key = take(sizeof(uint32_t) * n);
@@ -639,6 +639,7 @@ fmm_status make_plan(const fmm_params* prm, Shape&& sh, bool batch, void* d_work
     b.inst = reinterpret_cast<Inst*>(base + ly.inst);
     b.n_inst = pl->shape.n_inst;
     b.key_shift = 2 * pl->shape.Lmax;
+    b.seg_sort = seg_sort(pl->shape.n_cap, pl->shape.n_inst, b.key_shift);
     b.small_sort = small_sort(std::max(pl->shape.n_cap, pl->shape.m_cap), pl->shape.batched ? 0 : pl->shape.n_inst,
                               pl->shape.key_bits);
     pl->d_tables = reinterpret_cast<int32_t*>(base + ly.tables);
@@ -1005,7 +1006,7 @@ fmm_status fmm_get_status(fmm_plan_t plan, void* stream, int64_t* n_bad)
     *n_bad = 0;
     if (plan->last_n <= 0) return FMM_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const size_t nblk = size_t(radix_blocks(plan->last_n));
+    const size_t nblk = size_t(sort_tiles(plan->last_n, plan->buf.n_inst, plan->buf.seg_sort));
     const size_t tblk = size_t(radix_blocks(plan->last_m));
     std::vector<int32_t> per(nblk + tblk);
     if (hipMemcpyAsync(per.data(), plan->buf.bad_blk, nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st) !=

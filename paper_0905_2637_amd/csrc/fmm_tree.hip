@@ -197,6 +197,60 @@ __device__ __forceinline__ int particle_inst(const Inst* __restrict__ inst, int 
     return lo;
 }
 
+// The tiles of a radix pass.  One instance (or few particles an instance):
+// tile b holds the positions from 4096 b, and the instance is the key's
+// highest digits.  Segmented (kSegMinPer particles an instance and more): the
+// input and every pass keep the instances apart, so their digits are never
+// sorted.  Instance q owns the tiles from part_off[q] / 4096 + q on, at least
+// as many as it needs; a tile's records go to places of its own instance.
+// 512 instances of 2,048 to 65,536 particles, 10 leaf bits: two passes
+// instead of three and no search for a particle's instance, tree 760 -> 529 us.
+// Small instances would leave the tiles mostly empty; they sort by the whole
+// key.
+constexpr int kSegMinPer = 2 * kRadixTile;
+
+__device__ __forceinline__ int64_t seg_tile(const Inst* __restrict__ inst, int q)
+{
+    return inst[q].part_off / kRadixTile + q;
+}
+
+struct Tile {
+    int64_t base;      // first position
+    int n;             // positions (0: none)
+    int q;             // segmented: its instance,
+    int64_t first;     // the instance's first position
+    int t0, t1;        // and tiles [t0, t1)
+};
+
+template <bool SEG>
+__device__ __forceinline__ Tile tile_of(int blk, int n, const Inst* __restrict__ inst, int n_inst, int nblk)
+{
+    Tile t{};
+    if constexpr (!SEG) {
+        t.base = int64_t(blk) * kRadixTile;
+        t.n = int(max(int64_t(0), min(int64_t(kRadixTile), int64_t(n) - t.base)));
+        return t;
+    }
+    // the last instance whose tiles begin at or before blk, 64 probes a round
+    // (they ascend, and instance 0 begins at tile 0: lane 0 always says yes)
+    int lo = 0, hi = n_inst;
+    while (hi - lo > 1) {
+        const int step = (hi - lo + 63) / 64, i = lo + int(__lane_id()) * step;
+        const int below = __popcll(__ballot(i < hi && seg_tile(inst, i < hi ? i : lo) <= blk));
+        lo += (below - 1) * step;
+        hi = min(hi, lo + step);
+    }
+    t.q = __builtin_amdgcn_readfirstlane(lo);
+    t.first = inst[t.q].part_off;
+    t.t0 = int(seg_tile(inst, t.q));
+    const bool last = t.q + 1 == n_inst;
+    t.t1 = last ? nblk : int(seg_tile(inst, t.q + 1));
+    const int64_t end = last ? int64_t(n) : inst[t.q + 1].part_off;
+    t.base = t.first + int64_t(blk - t.t0) * kRadixTile;
+    t.n = int(max(int64_t(0), min(int64_t(kRadixTile), end - t.base)));
+    return t;
+}
+
 // The histogram kernels and the scatter take the same 4096-key tiles with
 // TPB-thread workgroups, 4096 / TPB keys per thread.  Few tiles (small n)
 // run with 1024 threads, so that every CU still holds many wavefronts to hide
@@ -207,7 +261,7 @@ __device__ __forceinline__ int particle_inst(const Inst* __restrict__ inst, int 
 // inspection), the out-of-domain count of the tile (every particle counts
 // when the domain is wider than kMaxWidth), and the tile's histogram of the
 // lowest digit.
-template <int TPB>
+template <int TPB, bool SEG>
 __global__ void __launch_bounds__(TPB)
 k_rhist_keys(int n, const double* __restrict__ x, const double* __restrict__ y, const Inst* __restrict__ inst,
              int n_inst, int key_shift, int nblk, uint32_t* __restrict__ key, int32_t* __restrict__ hist,
@@ -217,8 +271,8 @@ k_rhist_keys(int n, const double* __restrict__ x, const double* __restrict__ y, 
     constexpr int kTileRounds = kRadixTile / TPB;
     __shared__ int h[kRadixBins];
     __shared__ int nbad;
-    const int64_t base = int64_t(blockIdx.x) * kRadixTile;
-    if (base >= n) {             // a tile past the call's particles: empty (no input read)
+    const Tile tile = tile_of<SEG>(int(blockIdx.x), n, inst, n_inst, nblk);
+    if (tile.n == 0) {           // a tile without particles (no input read)
         if (threadIdx.x < kRadixBins) hist[int64_t(threadIdx.x) * nblk + blockIdx.x] = 0;
         if (threadIdx.x == 0) bad_blk[blockIdx.x] = 0;
         return;
@@ -230,17 +284,18 @@ k_rhist_keys(int n, const double* __restrict__ x, const double* __restrict__ y, 
     double xv[kTileRounds], yv[kTileRounds];
 #pragma unroll
     for (int r = 0; r < kTileRounds; ++r) {
-        const int64_t i = base + r * TPB + threadIdx.x;
-        const int64_t ic = i < n ? i : base;
+        const int li = r * TPB + int(threadIdx.x);
+        const int64_t ic = tile.base + (li < tile.n ? li : 0);
         xv[r] = x[ic];
         yv[r] = y[ic];
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kTileRounds; ++r) {
-        const int64_t i = base + r * TPB + threadIdx.x;
-        if (i < n) {
-            const int q = n_inst == 1 ? 0 : particle_inst(inst, n_inst, i);
+        const int li = r * TPB + int(threadIdx.x);
+        if (li < tile.n) {
+            const int64_t i = tile.base + li;
+            const int q = SEG ? tile.q : n_inst == 1 ? 0 : particle_inst(inst, n_inst, i);
             const int L = inst[q].L;
             const Domain d = inst[q].dom;
             const int side = 1 << L;
@@ -276,16 +331,16 @@ __device__ __forceinline__ KeyLeaf key_leaf(uint32_t k, const Inst* __restrict__
 }
 
 // Digit histogram of one tile, written digit-major: hist[d * nblk + block].
-template <int TPB>
+template <int TPB, bool SEG>
 __global__ void __launch_bounds__(TPB)
 k_rhist(int n, const uint32_t* __restrict__ kin, int shift, int nblk, int32_t* __restrict__ hist,
-        const int32_t* __restrict__ n_dev)
+        const Inst* __restrict__ inst, int n_inst, const int32_t* __restrict__ n_dev)
 {
     if (n_dev) n = *n_dev;
     constexpr int kTileRounds = kRadixTile / TPB;
     __shared__ int h[kRadixBins];
-    const int64_t base = int64_t(blockIdx.x) * kRadixTile;
-    if (base >= n) {             // a tile past the call's particles: empty
+    const Tile tile = tile_of<SEG>(int(blockIdx.x), n, inst, n_inst, nblk);
+    if (tile.n == 0) {
         if (threadIdx.x < kRadixBins) hist[int64_t(threadIdx.x) * nblk + blockIdx.x] = 0;
         return;
     }
@@ -293,14 +348,13 @@ k_rhist(int n, const uint32_t* __restrict__ kin, int shift, int nblk, int32_t* _
     uint32_t kv[kTileRounds];
 #pragma unroll
     for (int r = 0; r < kTileRounds; ++r) {
-        const int64_t i = base + r * TPB + threadIdx.x;
-        kv[r] = kin[i < n ? i : base];
+        const int li = r * TPB + int(threadIdx.x);
+        kv[r] = kin[tile.base + (li < tile.n ? li : 0)];
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kTileRounds; ++r) {
-        const int64_t i = base + r * TPB + threadIdx.x;
-        if (i < n) atomicAdd(&h[(kv[r] >> shift) & (kRadixBins - 1)], 1);
+        if (r * TPB + int(threadIdx.x) < tile.n) atomicAdd(&h[(kv[r] >> shift) & (kRadixBins - 1)], 1);
     }
     __syncthreads();
     if (threadIdx.x < kRadixBins) hist[int64_t(threadIdx.x) * nblk + blockIdx.x] = h[threadIdx.x];
@@ -330,17 +384,18 @@ struct Records {
 // Phase B stages each array through LDS in that order, so that consecutive
 // threads write consecutive addresses of each digit's run (offs[d * nblk +
 // block] is where the tile's run starts among digit d, total[d] the count of
-// digit d): whole cache lines
-// instead of scattered 8-byte writes.
+// digit d, both of the instance where segmented): whole cache lines instead of
+// scattered 8-byte writes.
 // iin == nullptr means the identity (first pass).  pk != nullptr (last pass,
 // mixed precision) also writes the FP32 leaf-relative record
 // (x - c, y - c) / w_L, gamma of the leaf centre c.
-template <int TPB>
+template <int TPB, bool SEG>
 __global__ void __launch_bounds__(TPB)
 k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__ iin,
            const double* __restrict__ xin, const double* __restrict__ yin, const double* __restrict__ gin,
            int shift, int nblk, const int32_t* __restrict__ hist, const int32_t* __restrict__ offs,
-           const int32_t* __restrict__ total, Records out, float4* __restrict__ pk, const Inst* __restrict__ inst, int key_shift, const int32_t* __restrict__ n_dev)
+           const int32_t* __restrict__ total, Records out, float4* __restrict__ pk, const Inst* __restrict__ inst, int n_inst,
+           int key_shift, const int32_t* __restrict__ n_dev)
 {
     if (n_dev) n = *n_dev;
     constexpr int kScatterThreads = TPB;
@@ -358,9 +413,10 @@ k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__
     // the runs of one digit that neighbouring tiles write side by side meet
     // in one L2 (whole lines go out) instead of leaving partial lines in two
     const int blk = nblk >= kScatterXcdMinTiles ? xcd_runs(int(blockIdx.x), nblk, kScatterXcdRun) : int(blockIdx.x);
-    const int64_t tile = int64_t(blk) * kRadixTile;
-    if (tile >= n) return;       // a tile past the call's particles: nothing to move
-    const int tile_n = int(min(int64_t(kRadixTile), int64_t(n) - tile));
+    const Tile seg = tile_of<SEG>(blk, n, inst, n_inst, nblk);
+    const int64_t tile = seg.base;
+    const int tile_n = seg.n;
+    if (tile_n == 0) return;
     constexpr int kWaveKeys = kRadixTile / kScatterWaves;
 
     // the tile's histogram (one digit per thread of the first 256) scanned
@@ -369,8 +425,14 @@ k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__
     int hv = 0, hinc = 0, go = 0, tv = 0, tinc = 0;
     if (tid < kRadixBins) {
         hv = hist[int64_t(tid) * nblk + blk];
-        go = offs[int64_t(tid) * nblk + blk];
+        const int32_t* row = offs + int64_t(tid) * nblk;
+        go = row[blk];
         tv = total[tid];
+        if constexpr (SEG) {     // the instance's share of the row
+            const int before = row[seg.t0];
+            tv = (seg.t1 < nblk ? row[seg.t1] : tv) - before;
+            go -= before;
+        }
         hinc = wave_incl_scan(hv);
         tinc = wave_incl_scan(tv);
         if (lane == 63) {
@@ -407,7 +469,7 @@ k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__
             start += q < w ? wsum[1][q] : 0;
         }
         tstart[tid] = before + hinc - hv;
-        gbase[tid] = start + tinc - tv + go;
+        gbase[tid] = int(seg.first) + start + tinc - tv + go;
     }
 
     // rank within the wavefront, round after round (input order): equal
@@ -888,20 +950,27 @@ bool small_sort(int64_t n_cap, int n_inst, int key_bits)
     return n_inst == 1 && key_bits >= 1 && key_bits <= kSmallKeyBits && radix_blocks(n_cap) <= kSmallTiles;
 }
 
-size_t hist_bytes(int64_t n_cap, int n_inst, int key_bits)
+bool seg_sort(int64_t n_cap, int n_inst, int key_shift)
 {
-    const size_t nblk = size_t(radix_blocks(n_cap));
-    const size_t passes = sizeof(int32_t) * kRadixBins * nblk;
-    const size_t small = small_sort(n_cap, n_inst, key_bits) ? (sizeof(uint16_t) << key_bits) * nblk : 0;
+    return n_inst > 1 && key_shift > 0 && n_cap >= int64_t(kSegMinPer) * n_inst;
+}
+
+int64_t sort_tiles(int64_t n, int n_inst, bool segmented)
+{
+    return segmented ? n / kRadixTile + n_inst : radix_blocks(n);
+}
+
+size_t hist_bytes(int64_t n_cap, int n_inst, int key_bits, int64_t tiles)
+{
+    const size_t passes = sizeof(int32_t) * kRadixBins * size_t(tiles);
+    const size_t small =
+        small_sort(n_cap, n_inst, key_bits) ? (sizeof(uint16_t) << key_bits) * size_t(radix_blocks(n_cap)) : 0;
     return passes > small ? passes : small;
 }
 
 namespace {
 
 // Radix passes of at most this many tiles use the 1024-thread kernels.
-#ifndef FMM_TREE_TPB
-#define FMM_TREE_TPB 0
-#endif
 constexpr int kWideTilesMax = 2048;
 
 void scan_table(const Buffers& b, int nblk, hipStream_t st)
@@ -914,13 +983,44 @@ void scan_table(const Buffers& b, int nblk, hipStream_t st)
 
 namespace {
 
+// The passes of a sort over the keys' lowest 8 npass bits.  first: whether the
+// first digit's histogram is there.
+void radix_sort(const Buffers& b, int n, int nblk, bool wide, bool seg, int npass, bool first, const uint32_t* kin,
+                const double* xin, const double* yin, const double* gin, const Records& fin, const Records& tmp,
+                float4* pk, hipStream_t st, const int32_t* n_dev)
+{
+    const int threads = wide ? 1024 : 256;
+    const auto count = seg ? (wide ? k_rhist<1024, true> : k_rhist<256, true>)
+                           : (wide ? k_rhist<1024, false> : k_rhist<256, false>);
+    const auto scatter = seg ? (wide ? k_rscatter<1024, true> : k_rscatter<256, true>)
+                             : (wide ? k_rscatter<1024, false> : k_rscatter<256, false>);
+    const uint32_t* iin = nullptr;
+    // the last pass writes the final arrays, the others alternate with tmp
+    for (int pass = 0; pass < npass; ++pass) {
+        const Records& out = ((npass - 1 - pass) & 1) ? tmp : fin;
+        const int shift = 8 * pass;
+        if (pass > 0 || !first)
+            hipLaunchKernelGGL(count, dim3(nblk), dim3(threads), 0, st, n, kin, shift, nblk, b.hist, b.inst, b.n_inst,
+                               n_dev);
+        scan_table(b, nblk, st);
+        hipLaunchKernelGGL(scatter, dim3(nblk), dim3(threads), 0, st, n, kin, iin, xin, yin, gin, shift, nblk, b.hist,
+                           b.hist_scan, b.scan_part, out, pass == npass - 1 ? pk : nullptr, b.inst, b.n_inst,
+                           b.key_shift, n_dev);
+        kin = out.k;
+        iin = out.idx;
+        xin = out.x;
+        yin = out.y;
+        gin = out.g;
+    }
+}
+
 // Keys, sort and leaf ranges of one point set: records (key, index, x, y and,
 // when g != nullptr, gamma), final arrays in fin, leaf ranges in leaf_start.
 void sort_points(const Buffers& b, int n, const double* x, const double* y, const double* g, uint32_t* key,
                  int32_t* bad_blk, const Records& fin, float4* pk, int32_t* leaf_start, int key_bits,
                  int64_t leaf_entries, hipStream_t st, const int32_t* n_dev = nullptr)
 {
-    const int nblk = int(radix_blocks(n));
+    const int nblk = int(sort_tiles(n, b.n_inst, b.seg_sort));
     if (b.small_sort) {
         // 16-bit counts of the wavefronts and a place per leaf in LDS, then (one tile) its records
         const size_t bins = size_t(1) << key_bits;
@@ -941,45 +1041,17 @@ void sort_points(const Buffers& b, int n, const double* x, const double* y, cons
         return;
     }
     const Records tmp{b.ktmp, b.itmp, b.xt, b.yt, g ? b.gt : nullptr};
-    const bool wide = FMM_TREE_TPB == 1024 || (FMM_TREE_TPB == 0 && nblk <= kWideTilesMax);
-    if (wide)
-        hipLaunchKernelGGL(k_rhist_keys<1024>, dim3(nblk), dim3(1024), 0, st, n, x, y, b.inst, b.n_inst,
-                           b.key_shift, nblk, key, b.hist, bad_blk, n_dev);
-    else
-        hipLaunchKernelGGL(k_rhist_keys<256>, dim3(nblk), dim3(256), 0, st, n, x, y, b.inst, b.n_inst,
-                           b.key_shift, nblk, key, b.hist, bad_blk, n_dev);
-    const int npass = radix_passes(key_bits);
-    if (npass == 0) {
+    const bool wide = nblk <= kWideTilesMax;
+    const int threads = wide ? 1024 : 256;
+    const auto keys = b.seg_sort ? (wide ? k_rhist_keys<1024, true> : k_rhist_keys<256, true>)
+                                 : (wide ? k_rhist_keys<1024, false> : k_rhist_keys<256, false>);
+    hipLaunchKernelGGL(keys, dim3(nblk), dim3(threads), 0, st, n, x, y, b.inst, b.n_inst, b.key_shift, nblk, key, b.hist,
+                       bad_blk, n_dev);
+    const int npass = radix_passes(b.seg_sort ? b.key_shift : key_bits);
+    if (npass == 0)
         hipLaunchKernelGGL(k_copy_one_leaf, dim3(blocks_for(n, 256)), dim3(256), 0, st, n, x, y, g, fin, pk, b.inst);
-    } else {
-        // the last pass writes the final arrays, the others alternate with tmp
-        const uint32_t* kin = key;
-        const uint32_t* iin = nullptr;
-        const double *xin = x, *yin = y, *gin = g;
-        for (int pass = 0; pass < npass; ++pass) {
-            const Records& out = ((npass - 1 - pass) & 1) ? tmp : fin;
-            const int shift = 8 * pass;
-            if (pass > 0 && wide)
-                hipLaunchKernelGGL(k_rhist<1024>, dim3(nblk), dim3(1024), 0, st, n, kin, shift, nblk, b.hist, n_dev);
-            else if (pass > 0)
-                hipLaunchKernelGGL(k_rhist<256>, dim3(nblk), dim3(256), 0, st, n, kin, shift, nblk, b.hist, n_dev);
-            scan_table(b, nblk, st);
-            const bool last = pass == npass - 1;
-            if (wide)
-                hipLaunchKernelGGL(k_rscatter<1024>, dim3(nblk), dim3(1024), 0, st, n, kin, iin, xin, yin, gin,
-                                   shift, nblk, b.hist, b.hist_scan, b.scan_part, out, last ? pk : nullptr, b.inst, b.key_shift,
-                                   n_dev);
-            else
-                hipLaunchKernelGGL(k_rscatter<256>, dim3(nblk), dim3(256), 0, st, n, kin, iin, xin, yin, gin,
-                                   shift, nblk, b.hist, b.hist_scan, b.scan_part, out, last ? pk : nullptr, b.inst, b.key_shift,
-                                   n_dev);
-            kin = out.k;
-            iin = out.idx;
-            xin = out.x;
-            yin = out.y;
-            gin = out.g;
-        }
-    }
+    else
+        radix_sort(b, n, nblk, wide, b.seg_sort, npass, true, key, x, y, g, fin, tmp, pk, st, n_dev);
     hipLaunchKernelGGL(k_bounds, dim3(blocks_for(int64_t(n) + 1, 256 * kBoundsRounds)), dim3(256), 0, st, n,
                        leaf_entries, fin.k, b.inst, b.n_inst, b.key_shift, leaf_start, n_dev);
 }
@@ -1012,30 +1084,7 @@ hipError_t launch_sort_keys(const Buffers& b, int n, const uint32_t* key, const 
     const int nblk = int(radix_blocks(n));
     const Records fin{ks, perm, xs, ys, gs};
     const Records tmp{b.ktmp, b.itmp, b.xt, b.yt, b.gt};
-    const bool wide = nblk <= kWideTilesMax;
-    const uint32_t* kin = key;
-    const uint32_t* iin = nullptr;
-    const double *xin = x, *yin = y, *gin = g;
-    for (int pass = 0; pass < npass; ++pass) {
-        const Records& out = ((npass - 1 - pass) & 1) ? tmp : fin;
-        const int shift = 8 * pass;
-        if (wide)
-            hipLaunchKernelGGL(k_rhist<1024>, dim3(nblk), dim3(1024), 0, st, n, kin, shift, nblk, b.hist, nullptr);
-        else
-            hipLaunchKernelGGL(k_rhist<256>, dim3(nblk), dim3(256), 0, st, n, kin, shift, nblk, b.hist, nullptr);
-        scan_table(b, nblk, st);
-        if (wide)
-            hipLaunchKernelGGL(k_rscatter<1024>, dim3(nblk), dim3(1024), 0, st, n, kin, iin, xin, yin, gin, shift,
-                               nblk, b.hist, b.hist_scan, b.scan_part, out, nullptr, nullptr, 0, nullptr);
-        else
-            hipLaunchKernelGGL(k_rscatter<256>, dim3(nblk), dim3(256), 0, st, n, kin, iin, xin, yin, gin, shift,
-                               nblk, b.hist, b.hist_scan, b.scan_part, out, nullptr, nullptr, 0, nullptr);
-        kin = out.k;
-        iin = out.idx;
-        xin = out.x;
-        yin = out.y;
-        gin = out.g;
-    }
+    radix_sort(b, n, nblk, nblk <= kWideTilesMax, false, npass, false, key, x, y, g, fin, tmp, nullptr, st, nullptr);
     return hipGetLastError();
 }
 
