@@ -970,8 +970,11 @@ size_t hist_bytes(int64_t n_cap, int n_inst, int key_bits, int64_t tiles)
 
 namespace {
 
-// Radix passes of at most this many tiles use the 1024-thread kernels.
-constexpr int kWideTilesMax = 2048;
+// Radix passes of at most this many tiles use the 1024-thread kernels: tree of
+// 10M particles 580 us with them, 637 with 256 threads; 16M 991 and 1042; 32M
+// 2002 and 1978; 64M 4316 and 3914.  (Batched evaluation of 9.7M, 2,880
+// tiles: 3181 and 3260 us.)
+constexpr int kWideTilesMax = 4096;
 
 void scan_table(const Buffers& b, int nblk, hipStream_t st)
 {
