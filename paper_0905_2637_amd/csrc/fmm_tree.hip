@@ -890,7 +890,11 @@ __device__ __forceinline__ int64_t leaf_entry(uint32_t k, const Inst* __restrict
 // A workgroup takes kBoundsRounds x 256 consecutive positions, 256 per round
 // (coalesced); all its key loads are issued before any range is written,
 // and a single-instance plan reads its instance record once.
+// A gap of kBoundsGap empty leaves and more is filled by the whole wavefront:
+// one thread's loop over a clustered tree's gaps took longer than all the key
+// loads (2^22 particles of 16 clusters, 2^18 leaves: 53 us, 14 here).
 constexpr int kBoundsRounds = 16;
+constexpr int kBoundsGap = 8;
 
 __global__ void __launch_bounds__(256)
 k_bounds(int n, int64_t entries, const uint32_t* __restrict__ ks, const Inst* __restrict__ inst, int n_inst,
@@ -919,10 +923,21 @@ k_bounds(int n, int64_t entries, const uint32_t* __restrict__ ks, const Inst* __
 #pragma unroll
     for (int r = 0; r < kBoundsRounds; ++r) {
         const int64_t i = base + int64_t(r) * 256;
-        if (i > n) break;
-        const int64_t lo = i == 0 ? 0 : entry(kp[r]) + 1;
-        const int64_t hi = i == n ? entries - 1 : entry(kc[r]);
-        for (int64_t e = lo; e <= hi; ++e) leaf_start[e] = int32_t(i);
+        if (__ballot(i <= n) == 0) break;
+        int lo = 0, hi = -1;                                // entries fit 31 bits
+        if (i <= n) {
+            lo = i == 0 ? 0 : int(entry(kp[r])) + 1;
+            hi = i == n ? int(entries) - 1 : int(entry(kc[r]));
+        }
+        const bool wide = hi - lo >= kBoundsGap;
+        if (!wide)
+            for (int e = lo; e <= hi; ++e) leaf_start[e] = int32_t(i);
+        for (uint64_t m = __ballot(wide); m != 0; m &= m - 1) {
+            const int l = __builtin_ctzll(m);
+            const int first = __builtin_amdgcn_readlane(lo, l), last = __builtin_amdgcn_readlane(hi, l);
+            const int32_t at = int32_t(i) + (l - int(__lane_id()));
+            for (int e = first + int(__lane_id()); e <= last; e += 64) leaf_start[e] = at;
+        }
     }
 }
 
