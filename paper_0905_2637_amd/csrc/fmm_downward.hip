@@ -492,93 +492,19 @@ struct M2LOut {
     cd* out[3];
 };
 
-// FP64 M2L with the sources of the workgroup's tile staged in LDS once: the
-// 16 x 16 target boxes of a workgroup (four child classes of an 8 x 8 parent
-// block) draw their interaction lists from the 20 x 20 boxes around them;
-// boxes outside the grid are staged as zeros.  Same classes and block order
-// as k_m2l_chunks, so the two give the same bits.  The stage takes
-// 6.4 KB per expansion term (109 KB at p = 17), which leaves room for one
-// workgroup per CU: on grids of a few tens of workgroups it is the faster
-// (the whole stage loaded once); on larger ones the chunked stage, whose
-// smaller footprint lets more wavefronts hide the loads.
-constexpr int kM2LStageMaxWg = 32;
-template <int P>
-__global__ void __launch_bounds__(256)
-k_m2l64_lds(Work wk, int n_inst, const Inst* __restrict__ inst, const cd* __restrict__ me_all, M2LOut dst_,
-            const cplx<double>* __restrict__ H, const double* __restrict__ sout_)
-{
-    __shared__ cd sA[(kHalo * kHalo + 1) * P];        // + a box of zeros
-    const int lin = xcd_runs(int(blockIdx.x + gridDim.x * blockIdx.y), int(gridDim.x * gridDim.y), kM2LXcdRun);
-    const int g = lin / int(gridDim.x), blk = lin % int(gridDim.x);
-    if (blk >= wk.wg_begin[n_inst]) return;                // past the launch's work (batched plans)
-    const int pos = find_inst(wk.wg_begin, n_inst, blk);
-    const int q = wk.order[pos];
-    const int G = min(int(gridDim.y), inst[q].g64);
-    if (g >= G) return;
-    int bl = blk - wk.wg_begin[pos];
-    int l = wk.arg[2 * pos];
-    while (bl >= level_blocks(l)) { bl -= level_blocks(l); ++l; }
-    const cd* me = me_all + inst[q].box_off * P;
-    cd* __restrict__ le = g == 0 ? dst_.out[0] + inst[q].box_off * P : dst_.out[g] + inst[q].split_off * P;
-    const int side = 1 << l;
-    const int bpr = side >= 16 ? side / 16 : 1;
-    const int bx = bl % bpr, by = bl / bpr;
-    const cd* me_l = me + level_offset(l) * P;
-    const int x_lo = 16 * bx - 2, y_lo = 16 * by - 2;
-    // eight loads in flight per thread before their LDS writes
-    for (int e0 = threadIdx.x; e0 < kHalo * kHalo * P; e0 += 256 * 8) {
-        cd v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = e0 + 256 * u, hb = e / P, k = e - hb * P;
-            const int sa = x_lo + hb % kHalo, sb = y_lo + hb / kHalo;
-            const bool in = e < kHalo * kHalo * P && sa >= 0 && sb >= 0 && sa < side && sb < side;
-            v[u] = me_l[in ? int64_t(morton(uint32_t(sa), uint32_t(sb))) * P + k : 0];
-            if (!in) v[u] = cd{0.0, 0.0};
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (e0 + 256 * u < kHalo * kHalo * P) sA[e0 + 256 * u] = v[u];
-    }
-    for (int k = threadIdx.x; k < P; k += 256) sA[kHalo * kHalo * P + k] = cd{0.0, 0.0};
-    __syncthreads();
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const int cx = wave & 1, cy = wave >> 1;
-    const int ta = 2 * (bx * 8 + (lane & 7)) + cx;
-    const int tb = 2 * (by * 8 + (lane >> 3)) + cy;
-    const bool active = ta < side && tb < side;
-    double bx_[P], by_[P];
-#pragma unroll
-    for (int k = 0; k < P; ++k) { bx_[k] = 0.0; by_[k] = 0.0; }
-    // the classes block by block, in the order of k_m2l_chunks
-    const int mine = (tb - y_lo) * kHalo + (ta - x_lo);
-    auto term = [&](int sl, int k) { return sA[sl * P + k]; };
-    const int mask = m2l_class_mask(g, G);
-    m2l_for_chunks([&](auto c) {
-        m2l_classes<P, decltype(c)::value * kM2LClassK, kM2LClassK>(bx_, by_, H, cx, cy, mask, mine, term);
-    }, std::make_integer_sequence<int, (P + kM2LClassK - 1) / kM2LClassK>{});
-    if (active) {
-        cd* dst = le + (level_offset(l) + int64_t(morton(uint32_t(ta), uint32_t(tb)))) * P;
-#pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const double sc = sout_[k];
-            dst[k] = cd{bx_[k] * sc, by_[k] * sc};
-        }
-    }
-}
-
-// M2L by symmetry classes (T = double: every FP64 level but the smallest
-// launches; P = 32 by pairs) and by symmetric pairs (T = float: the FP32 levels
-// of the mixed form on the vector units) with the workgroup's sources staged in LDS kM2LK terms at a time:
-// the 16 x 16 targets of a workgroup draw every source from the 20 x 20
-// boxes around them, so chunk c holds terms 4c .. 4c + 3 of those 400 boxes
-// (25.6 KB in FP64, k-major, zeros outside the level and past p, one zero
-// box at the end for the item without a partner) and every wavefront runs
-// block c of all its work items or classes from it.  The loads of a chunk are
-// coalesced and shared by the workgroup's 256 targets instead of issued per
-// lane and member; in FP64 the same classes and block order as k_m2l64_lds,
-// so the two give the same bits.
+// M2L by symmetry classes (T = double; P = 32 by pairs) and by symmetric pairs
+// (T = float: the FP32 levels of the mixed form on the vector units) with the
+// workgroup's sources staged in LDS kM2LK terms at a time: the 16 x 16 targets
+// of a workgroup draw every source from the 20 x 20 boxes around them, so chunk
+// c holds terms 4c .. 4c + 3 of those 400 boxes (25.6 KB in FP64, k-major,
+// zeros outside the level and past p, one zero box at the end for the item
+// without a partner) and every wavefront runs block c of all its work items or
+// classes from it.  The loads of a chunk are coalesced and shared by the
+// workgroup's 256 targets instead of issued per lane and member.  A kernel that
+// stages every term at once served launches of few workgroups while the pairs
+// took most of their time; with the classes the chunks are the faster there too
+// (4,096 particles, depth 4: P = 8 18.6 us whole, 11.5 in chunks; 12 19.1 and
+// 16.0; 17 23.3 and 23.9; 20 31.3 and 27.9), and it is gone.
 template <int P, typename T>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(std::is_same<T, double>::value ? 2 : 3)))
 k_m2l_chunks(Work wk, int n_inst, const Inst* __restrict__ inst, const cd* __restrict__ me_all, M2LOut dst_,
@@ -1074,13 +1000,6 @@ hipError_t m2l_impl(const Buffers& b, const Work& w, int nwg, bool fp32, bool mf
         if (fp32) {
             hipLaunchKernelGGL((k_m2l_chunks<P, float>), grid, dim3(256), 0, st, w, b.n_inst, b.inst, b.me, out,
                                reinterpret_cast<const cplx<float>*>(b.t_h32), b.t_sout);
-            return hipGetLastError();
-        }
-    }
-    if constexpr (P <= 20) {       // beyond, the staged form spills registers
-        if (int64_t(nwg) * groups <= kM2LStageMaxWg) {
-            hipLaunchKernelGGL((k_m2l64_lds<P>), grid, dim3(256), 0, st, w, b.n_inst, b.inst, b.me, out,
-                               reinterpret_cast<const cplx<double>*>(b.t_h64), b.t_sout);
             return hipGetLastError();
         }
     }

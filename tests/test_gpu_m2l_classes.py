@@ -1,8 +1,8 @@
 """The FP64 M2L by the symmetry classes of the square: every local coefficient
 of every level against the oracle's, order by order (an error in a high order
 does not reach the velocities), at each compiled expansion size and the padded
-ones next to it, on the two kernels (few workgroups: sources staged whole; more:
-in chunks of terms) and with the list in one part and split.
+ones next to it, on launches of one workgroup and of many, and with the list in
+one part and split.
 
 Tolerance: the largest difference of an order on a level, relative to that
 order's largest coefficient there, below 1e-11, the bound that the coefficient
