@@ -198,7 +198,7 @@ fmm_status batch_shape(const fmm_params* prm, Shape& sh, int64_t& max_leaves)
 }
 
 struct Layout {
-    size_t inst, tables, bad_blk, bbox, leaf_start, hist, hist_scan, scan_part;
+    size_t inst, tables, bad_blk, bbox, leaf_start, hist, hist_scan;
     size_t key, ksorted, perm, xs, ys, gs, ktmp, itmp, xt, yt, gt, pk, blk_tab, me, le, le_part[2];
     size_t tkey, tks, tperm, txs, tys, tleaf_start, tbad;
     size_t fgt_a, fgt_b, fgt_h;
@@ -223,7 +223,6 @@ Layout make_layout(const Shape& sh, int P, bool mixed)
     ly.leaf_start = take(sizeof(int32_t) * size_t(sh.leaf_entries));
     ly.hist = take(hist_bytes(int64_t(nm), sh.batched ? 0 : sh.n_inst, sh.key_bits, int64_t(nblk)));
     ly.hist_scan = take(sizeof(int32_t) * kHistDigits * nblk);
-    ly.scan_part = take(sizeof(int32_t) * kHistDigits);
     ly.key = take(sizeof(uint32_t) * n);
     ly.ksorted = take(sizeof(uint32_t) * n);
     ly.perm = take(sizeof(uint32_t) * n);
@@ -251,7 +250,7 @@ Layout make_layout(const Shape& sh, int P, bool mixed)
     ly.le_part[1] = take(sizeof(cd) * size_t(sh.split_boxes) * P);
     ly.t_m2m = take(sizeof(cd) * 4 * P * P);
     ly.t_l2l = take(sizeof(cd) * 4 * P * P);
-    ly.t_h64 = take(sizeof(cd) * kHankelGrid * kHankelGrid * hankel_row(P));
+    ly.t_h64 = take(sizeof(cd) * kHankelGrid * kHankelGrid * (2 * P - 1));
     ly.t_h32 = take(sizeof(cf) * kHankelGrid * kHankelGrid * (2 * P - 1));
     ly.t_sin = take(sizeof(double) * P);
     ly.t_sout = take(sizeof(double) * P);
@@ -648,7 +647,7 @@ fmm_status make_plan(const fmm_params* prm, Shape&& sh, bool batch, void* d_work
     b.leaf_start = reinterpret_cast<int32_t*>(base + ly.leaf_start);
     b.hist = reinterpret_cast<int32_t*>(base + ly.hist);
     b.hist_scan = reinterpret_cast<int32_t*>(base + ly.hist_scan);
-    b.scan_part = reinterpret_cast<int32_t*>(base + ly.scan_part);
+    b.scan_part = reinterpret_cast<int32_t*>(b.bbox);   // reduced before the sort
     b.key = reinterpret_cast<uint32_t*>(base + ly.key);
     b.ksorted = reinterpret_cast<uint32_t*>(base + ly.ksorted);
     b.perm = reinterpret_cast<uint32_t*>(base + ly.perm);
@@ -694,8 +693,7 @@ fmm_status make_plan(const fmm_params* prm, Shape&& sh, bool batch, void* d_work
     b.fgt_h = fgt ? reinterpret_cast<double*>(base + ly.fgt_h) : nullptr;
 
     const size_t nh = size_t(kHankelGrid) * kHankelGrid * (2 * P - 1);
-    std::vector<cd> m2m(size_t(4) * P * P), l2l(size_t(4) * P * P);
-    std::vector<cd> h64(size_t(kHankelGrid) * kHankelGrid * hankel_row(P));
+    std::vector<cd> m2m(size_t(4) * P * P), l2l(size_t(4) * P * P), h64(nh);
     std::vector<cf> h32(nh);
     std::vector<double> sin_(P), sout_(P);
     build_tables(P, prm->p, m2m.data(), l2l.data(), h64.data(), h32.data(), sin_.data(), sout_.data());

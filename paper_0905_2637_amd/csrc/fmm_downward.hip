@@ -366,7 +366,7 @@ __device__ __forceinline__ void m2l_classes(double* bx, double* by, const cplx<d
 {
     const int sx = cx ? -1 : 1, sy = cy ? -1 : 1;
     const double s = double(sx * sy);
-    const auto data = [&](int a, int b) { return H + ((sy * b + 3) * kHankelGrid + (sx * a + 3)) * hankel_row(P); };
+    const auto data = [&](int a, int b) { return H + ((sy * b + 3) * kHankelGrid + (sx * a + 3)) * (2 * P - 1); };
     // the 27 addresses are formed again for every block: kept, they would take
     // 27 registers
     asm volatile("" : "+v"(mine));

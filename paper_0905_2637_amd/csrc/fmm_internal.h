@@ -33,14 +33,16 @@ constexpr int kMaxDepth = 13;
 constexpr int kMaxP = 32;
 constexpr int kMaxPMixed = 22;      // FP32 translation data overflows beyond this
 constexpr int kHankelGrid = 7;      // integer M2L offsets (dx, dy) with |dx|, |dy| <= 3
-// A row of the FP64 translation data h_0 .. h_(2P-2): residue by residue of n
-// mod 4 for the M2L by symmetry classes (P <= 24; beyond, its operands do not
-// fit the registers), else in order.
+// Place of h_n in a row h_0 .. h_(2P-2) of the FP64 translation data: residue
+// by residue of n mod 4 for the M2L by symmetry classes (P <= 24; beyond, its
+// operands do not fit the registers), else in order.
 __host__ __device__ constexpr bool hankel_by_residue(int P) { return P <= 24; }
-__host__ __device__ constexpr int hankel_row(int P) { return hankel_by_residue(P) ? (2 * P + 2) / 4 * 4 : 2 * P - 1; }
 __host__ __device__ constexpr int hankel_slot(int P, int n)
 {
-    return hankel_by_residue(P) ? (n % 4) * (hankel_row(P) / 4) + n / 4 : n;
+    if (!hankel_by_residue(P)) return n;
+    int before = 0;
+    for (int r = 0; r < n % 4; ++r) before += (2 * P + 2 - r) / 4;      // how many n = r mod 4
+    return before + n / 4;
 }
 constexpr int kBBoxBlocks = 256;
 constexpr int kMaxInstances = 1 << 16;
@@ -159,7 +161,7 @@ struct Buffers {
     bool small_sort;       // the particles (and target points) sort in one pass over the whole key
     int32_t* hist;         // [256 * sort_tiles] digit-major tile histograms (hist_bytes)
     int32_t* hist_scan;    // [256 * sort_tiles] exclusive scans of its rows
-    int32_t* scan_part;    // [256] and the rows' totals
+    int32_t* scan_part;    // [256] the rows' totals (2D plans: over bbox)
     uint32_t* key;         // [n_max] instance and leaf key per input particle
     uint32_t* ksorted;     // [n_max] sorted keys
     uint32_t* perm;        // [n_max] sorted position -> input index
@@ -187,7 +189,7 @@ struct Buffers {
     cd* le_part[2];        // [sum Lambda(split)_i * P] partial M2L sums of the split levels
     cd* t_m2m;             // [4][P][P]
     cd* t_l2l;             // [4][P][P]
-    cd* t_h64;             // [49][hankel_row(P)] M2L translation data, FP64
+    cd* t_h64;             // [49][2P-1] M2L translation data, FP64 (hankel_slot)
     cf* t_h32;             // [49][2P-1] M2L translation data, FP32
     double* t_sin;         // [P] (-1)^(k+1) / k!
     double* t_sout;        // [P] 1 / l!

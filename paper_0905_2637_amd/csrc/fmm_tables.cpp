@@ -74,7 +74,7 @@ void build_tables(int P, int p, cd* m2m, cd* l2l, cd* h64, cf* h32, double* sin_
             long double fact = 1.0L;     // n!
             for (int n = 0; n < nh; ++n) {
                 cld h = (used && n <= 2 * p - 2) ? fact * t : cld(0.0L, 0.0L);
-                h64[slot * hankel_row(P) + hankel_slot(P, n)] = to_cd(h);
+                h64[slot * nh + hankel_slot(P, n)] = to_cd(h);
                 h32[slot * nh + n] = cf{float(h.real()), float(h.imag())};
                 t *= inv;
                 fact *= (long double)(n + 1);
