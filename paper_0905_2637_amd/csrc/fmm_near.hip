@@ -165,32 +165,49 @@ constexpr int kR = 4;              // most targets per lane
 // targets a lane owns.  FP32 leaf-relative form: coordinates in leaf widths,
 // exp(-t) = 2^(-t log2 e) with c2 = w^2 log2(e) / (2 sigma^2).  The singular
 // kernel of eq. 7 has no Gaussian factor.  (No Lennard-Jones form in FP32.)
+// Two sources a round, the next ones' reads in flight during the pairs: held
+// to 72 registers the compiler otherwise waits for every read at its use,
+// which a SIMD of few wavefronts cannot hide (Gaussian, 64 leaves of 1,000:
+// 5.50 ms without, 4.79 with; 4^8 leaves of 44: 728 and 703 us).
 template <int R, int KER>
 __device__ __forceinline__ void p2p_f32(const float4* __restrict__ src, int cnt, int S, int si, float c2,
                                         const float* ox, const float* oy, float* fx, float* fy)
 {
-#pragma unroll 2
-    for (int jb = 0; jb < cnt; jb += S) {
-        const float4 t = src[jb + si];
+    const auto pairs = [&](const float4 t) {
+        float dx[R], dy[R], q2[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const float dx = ox[r] - t.x, dy = oy[r] - t.y;
-            float q2;
+            dx[r] = ox[r] - t.x;
+            dy[r] = oy[r] - t.y;
+            // Gaussian: > 0 for coincident points, whose term is then 0 through 1 - e = 0
+            q2[r] = fmaf(dx[r], dx[r], KER == kNearSingular ? dy[r] * dy[r] : fmaf(dy[r], dy[r], 1e-30f));
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
             if constexpr (KER == kNearSingular) {
                 // a select, not a guard term: gamma / guard would overflow
                 // for large circulations and the product with dx = 0 give NaN
-                const float r2 = fmaf(dx, dx, dy * dy);
-                q2 = r2 > 0.0f ? t.z * __builtin_amdgcn_rcpf(r2) : 0.0f;
+                q2[r] = q2[r] > 0.0f ? t.z * __builtin_amdgcn_rcpf(q2[r]) : 0.0f;
             } else {
-                // > 0 for coincident points, whose term is then 0 through 1 - e = 0
-                const float r2 = fmaf(dx, dx, fmaf(dy, dy, 1e-30f));
-                const float e = __builtin_amdgcn_exp2f(-r2 * c2);
-                q2 = fmaf(-t.z, e, t.z) * __builtin_amdgcn_rcpf(r2);
+                const float e = __builtin_amdgcn_exp2f(-q2[r] * c2);
+                q2[r] = fmaf(-t.z, e, t.z) * __builtin_amdgcn_rcpf(q2[r]);
             }
-            fx[r] = fmaf(q2, dx, fx[r]);
-            fy[r] = fmaf(-q2, dy, fy[r]);
         }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            fx[r] = fmaf(q2[r], dx[r], fx[r]);
+            fy[r] = fmaf(-q2[r], dy[r], fy[r]);
+        }
+    };
+    int jb = 0;
+    float4 t0 = src[si];
+    for (; jb + S < cnt; jb += 2 * S) {
+        const float4 t1 = src[jb + S + si];
+        pairs(t0);
+        t0 = src[min(jb + 2 * S, kNearStage - S) + si];   // past cnt: read within the stage, not used
+        pairs(t1);
     }
+    if (jb < cnt) pairs(t0);
 }
 
 // Lennard-Jones pair term -V'(r) / r = 24 eps (2 (s/r)^12 - (s/r)^6) / r^2 for
