@@ -695,6 +695,30 @@ constexpr int kEvalSrc3 = 256;        // sources staged at a time per wavefront
 constexpr int kEvalWaves3 = 4;
 constexpr int kEvalTail3 = 64;        // workgroups that clear the outputs of particles outside the cube
 
+// One pair's term added to a target's sums.  About 25 vector instructions
+// beside the reciprocal root: the hardware estimate (within 2^-24) and one
+// third-order step y (1 + e/2 + 3 e^2 / 8), e = 1 - r2 y^2, which leaves
+// rounding only.  Pairs at zero distance, and those whose r2 overflows (their
+// terms vanish), are left out by class.  EXACT: the charge may be infinite or
+// NaN, so a pair at zero distance is kept out of the product with it too.
+template <bool EXACT>
+__device__ __forceinline__ void pair3(double dx, double dy, double dz, double w, double& f, double& fx, double& fy,
+                                      double& fz)
+{
+    const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+    const double y0 = __builtin_amdgcn_rsq(r2);
+    const double e = fma(-(r2 * y0), y0, 1.0);
+    const double y1 = fma(y0 * e, fma(e, 0.375, 0.5), y0);
+    const bool ok = __builtin_amdgcn_class(r2, 0x180);       // positive normal or subnormal
+    const double ir = ok ? y1 : 0.0;
+    const double qr = EXACT && r2 == 0.0 ? 0.0 : w * ir;
+    const double cc = qr * ir * ir;
+    f += qr;
+    fx = fma(-cc, dx, fx);
+    fy = fma(-cc, dy, fy);
+    fz = fma(-cc, dz, fz);
+}
+
 // R targets per lane; TG = ceil(t / R) lanes make a group that holds all t
 // targets of a chunk, S = 64 / TG groups share the sources.  Adds the pairs of
 // `cnt` staged sources (a multiple of S, padded with sources of charge zero).
@@ -703,28 +727,10 @@ __device__ __forceinline__ void near3(const double4* __restrict__ src, int cnt, 
                                       const double (&y)[R], const double (&z)[R], double (&f)[R], double (&fx)[R],
                                       double (&fy)[R], double (&fz)[R])
 {
-    // About 25 vector instructions a pair beside the reciprocal root: the hardware
-    // estimate (within 2^-24) and one third-order step y (1 + e/2 + 3 e^2 / 8),
-    // e = 1 - r2 y^2, which leaves rounding only.  Pairs at zero distance, and
-    // those whose r2 overflows (their terms vanish), are left out by class.
     for (int j = slice; j < cnt; j += S) {
         const double4 s = src[j];
 #pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const double dx = x[i] - s.x, dy = y[i] - s.y, dz = z[i] - s.z;
-            const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-            const double y0 = __builtin_amdgcn_rsq(r2);
-            const double e = fma(-(r2 * y0), y0, 1.0);
-            const double y1 = fma(y0 * e, fma(e, 0.375, 0.5), y0);
-            const bool ok = __builtin_amdgcn_class(r2, 0x180);       // positive normal or subnormal
-            const double ir = ok ? y1 : 0.0;
-            const double qr = s.w * ir;
-            const double cc = qr * ir * ir;
-            f[i] += qr;
-            fx[i] = fma(-cc, dx, fx[i]);
-            fy[i] = fma(-cc, dy, fy[i]);
-            fz[i] = fma(-cc, dz, fz[i]);
-        }
+        for (int i = 0; i < R; ++i) pair3<false>(x[i] - s.x, y[i] - s.y, z[i] - s.z, s.w, f[i], fx[i], fy[i], fz[i]);
     }
 }
 
@@ -809,9 +815,31 @@ __device__ __forceinline__ void chunk3(double4 s, int t0, int t, int part, int n
             v[q] = double4{xs[j], ys[j], zs[j], 64 * q + lane < cnt ? qs[j] : 0.0};
         }
         wave_sync3();
+        bool bad = false;
 #pragma unroll
-        for (int q = 0; q < kEvalSrc3 / 64; ++q) buf[64 * q + lane] = v[q];
+        for (int q = 0; q < kEvalSrc3 / 64; ++q) {
+            buf[64 * q + lane] = v[q];
+            bad = bad || __builtin_amdgcn_class(v[q].w, 0x207);
+        }
         wave_sync3();
+        // Infinite and NaN charges act here, one after another, and are zero from
+        // then on: times the zero of a coincident pair (a particle and itself)
+        // they would be NaN, and a select in near3 costs every call 1.5 to 3 %
+        // (octree of 2^20 charges, p = 6: 1486 us without, 1511 and 1535 with).
+        if (__ballot(bad) != 0) {
+#pragma unroll 1
+            for (int j = 0; j < kEvalSrc3; ++j) {
+                const double4 c = buf[j];
+                if (!__builtin_amdgcn_class(c.w, 0x207)) continue;
+                if (slice == 0)
+#pragma unroll
+                    for (int i = 0; i < R; ++i)
+                        pair3<true>(x[i] - c.x, y[i] - c.y, z[i] - c.z, c.w, f[i], fx[i], fy[i], fz[i]);
+                wave_sync3();
+                buf[j].w = 0.0;
+                wave_sync3();
+            }
+        }
         if (live) near3<R>(buf, min(kEvalSrc3, (cnt + S - 1) / S * S), slice, S, x, y, z, f, fx, fy, fz);
     }
     // sums of the slices (and, WPL > 1, of the leaf's wavefronts) in order
