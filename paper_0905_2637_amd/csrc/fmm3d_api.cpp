@@ -16,7 +16,7 @@ namespace {
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 struct Layout3 {
-    size_t hist, hist_scan, scan_part, ktmp, itmp, xt, yt, gt;
+    size_t hist, scan_part, ktmp, itmp, xt, yt, gt;
     size_t key, ks, perm, xs, ys, zs, qs, leaf_start, me, mt, le, op, term, nbad;
     size_t total;
 };
@@ -43,7 +43,6 @@ Layout3 layout3(const fmm3d_params* prm)
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = align256(off + bytes); return o; };
     ly.hist = take(sizeof(int32_t) * nhist);
-    ly.hist_scan = take(sizeof(int32_t) * nhist);
     ly.scan_part = take(sizeof(int32_t) * fmm::kHistDigits);
     ly.ktmp = take(sizeof(uint32_t) * n);
     ly.itmp = take(sizeof(uint32_t) * n);
@@ -235,7 +234,6 @@ fmm_status fmm3d_plan(const fmm3d_params* prm, void* d_workspace, size_t bytes, 
     Bufs3& b = pl->buf;
     b.sort = fmm::Buffers{};
     b.sort.hist = static_cast<int32_t*>(at(ly.hist));
-    b.sort.hist_scan = static_cast<int32_t*>(at(ly.hist_scan));
     b.sort.scan_part = static_cast<int32_t*>(at(ly.scan_part));
     b.sort.ktmp = static_cast<uint32_t*>(at(ly.ktmp));
     b.sort.itmp = static_cast<uint32_t*>(at(ly.itmp));

@@ -109,7 +109,7 @@ struct Geo3 {
 };
 
 struct Bufs3 {
-    fmm::Buffers sort;          // radix temporaries only (hist, hist_scan, scan_part, ktmp, itmp, xt, yt, gt)
+    fmm::Buffers sort;          // radix temporaries only (hist, scan_part, ktmp, itmp, xt, yt, gt)
     uint32_t* key;              // [n_max] leaf key per input particle (2^(3L) outside the cube)
     uint32_t* ks;               // [n_max] sorted keys
     uint32_t* perm;             // [n_max] sorted position -> input index

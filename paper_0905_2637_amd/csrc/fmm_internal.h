@@ -159,8 +159,7 @@ struct Buffers {
     int32_t* leaf_start;   // [sum (4^L_i + 1)] sorted ranges of every leaf of every instance
     bool seg_sort;         // the instances are sorted apart, by the leaf bits only
     bool small_sort;       // the particles (and target points) sort in one pass over the whole key
-    int32_t* hist;         // [256 * sort_tiles] digit-major tile histograms (hist_bytes)
-    int32_t* hist_scan;    // [256 * sort_tiles] exclusive scans of its rows
+    int32_t* hist;         // [256 * sort_tiles] digit-major tile histograms, then their rows' exclusive scans
     int32_t* scan_part;    // [256] the rows' totals (2D plans: over bbox)
     uint32_t* key;         // [n_max] instance and leaf key per input particle
     uint32_t* ksorted;     // [n_max] sorted keys
@@ -204,10 +203,8 @@ struct Buffers {
 // bits, and workgroup tiles of 4096 keys.
 int radix_passes(int key_bits);
 int64_t radix_blocks(int64_t n);
-// whether a plan of this capacity sorts in one pass over the whole key, and
-// the bytes of its histograms
+// whether a plan of this capacity sorts in one pass over the whole key
 bool small_sort(int64_t n_cap, int n_inst, int key_bits);
-size_t hist_bytes(int64_t n_cap, int n_inst, int key_bits, int64_t tiles);
 // whether a plan of this capacity keeps its instances apart in the sort, and
 // the tiles of a sort of n records (a plan's capacity where segmented)
 bool seg_sort(int64_t n_cap, int n_inst, int key_shift);

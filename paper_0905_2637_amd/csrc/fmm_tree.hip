@@ -138,26 +138,26 @@ __device__ __forceinline__ int wave_incl_scan(int v)
 }
 
 // Histogram table of a radix pass, digit-major [256][nblk]: one workgroup per
-// digit scans its row into out (exclusive) and writes the digit's total; the
-// scatter turns the 256 totals into the digits' starts itself.  A wavefront
-// takes a run of the row, 64 tiles a round.  Latency-bound: 4.7 us a pass on
-// 256 tiles and 14 us on 16,384, against 9.5 and 30 us for a two-level scan
-// of the whole table by two kernels.
+// digit scans its row in place (exclusive) and writes the digit's total; the
+// scatter turns the 256 totals into the digits' starts itself, and takes a
+// tile's count as the difference to the next entry.  A wavefront takes a run of
+// the row, 64 tiles a round, four rounds' loads at once.  Latency-bound: 4.7 us
+// a pass on 256 tiles and 14 us on 16,384, against 9.5 and 30 us for a
+// two-level scan of the whole table by two kernels.
 constexpr int kRowScanThreads = 1024;
 constexpr int kRowScanWaves = kRowScanThreads / 64;
 
 __global__ void __launch_bounds__(kRowScanThreads)
-k_scan_rows(int nblk, const int32_t* __restrict__ in, int32_t* __restrict__ out, int32_t* __restrict__ total)
+k_scan_rows(int nblk, int32_t* __restrict__ table, int32_t* __restrict__ total)
 {
     __shared__ int wsum[kRowScanWaves];
     const int lane = __lane_id(), w = threadIdx.x >> 6;
     const int run_tiles = ((nblk + kRowScanThreads - 1) / kRowScanThreads) * 64;
     const int b0 = min(nblk, w * run_tiles), b1 = min(nblk, b0 + run_tiles);
-    const int32_t* src = in + int64_t(blockIdx.x) * nblk;
-    int32_t* dst = out + int64_t(blockIdx.x) * nblk;
+    int32_t* row = table + int64_t(blockIdx.x) * nblk;
     int s = 0;
 #pragma unroll 8
-    for (int b = b0 + lane; b < b1; b += 64) s += src[b];
+    for (int b = b0 + lane; b < b1; b += 64) s += row[b];
     s = wave_incl_scan(s);
     if (lane == 63) wsum[w] = s;
     __syncthreads();
@@ -167,12 +167,21 @@ k_scan_rows(int nblk, const int32_t* __restrict__ in, int32_t* __restrict__ out,
         run += k < w ? wsum[k] : 0;
         all += wsum[k];
     }
-#pragma unroll 4
-    for (int c = b0; c < b1; c += 64) {
-        const int b = c + lane, v = b < b1 ? src[b] : 0;
-        const int inc = wave_incl_scan(v);
-        if (b < b1) dst[b] = run + inc - v;
-        run += __builtin_amdgcn_readlane(inc, 63);
+    for (int c = b0; c < b1; c += 256) {
+        int v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int b = c + 64 * r + lane;
+            v[r] = b < b1 ? row[b] : 0;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (c + 64 * r >= b1) break;
+            const int b = c + 64 * r + lane;
+            const int inc = wave_incl_scan(v[r]);
+            if (b < b1) row[b] = run + inc - v[r];
+            run += __builtin_amdgcn_readlane(inc, 63);
+        }
     }
     if (threadIdx.x == 0) total[blockIdx.x] = all;
 }
@@ -384,8 +393,8 @@ struct Records {
 // Phase B stages each array through LDS in that order, so that consecutive
 // threads write consecutive addresses of each digit's run (offs[d * nblk +
 // block] is where the tile's run starts among digit d, total[d] the count of
-// digit d, both of the instance where segmented): whole cache lines instead of
-// scattered 8-byte writes.
+// digit d; where segmented, both less those of the instances before): whole
+// cache lines instead of scattered 8-byte writes.
 // iin == nullptr means the identity (first pass).  pk != nullptr (last pass,
 // mixed precision) also writes the FP32 leaf-relative record
 // (x - c, y - c) / w_L, gamma of the leaf centre c.
@@ -393,8 +402,8 @@ template <int TPB, bool SEG>
 __global__ void __launch_bounds__(TPB)
 k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__ iin,
            const double* __restrict__ xin, const double* __restrict__ yin, const double* __restrict__ gin,
-           int shift, int nblk, const int32_t* __restrict__ hist, const int32_t* __restrict__ offs,
-           const int32_t* __restrict__ total, Records out, float4* __restrict__ pk, const Inst* __restrict__ inst, int n_inst,
+           int shift, int nblk, const int32_t* __restrict__ offs, const int32_t* __restrict__ total,
+           Records out, float4* __restrict__ pk, const Inst* __restrict__ inst, int n_inst,
            int key_shift, const int32_t* __restrict__ n_dev)
 {
     if (n_dev) n = *n_dev;
@@ -424,10 +433,10 @@ k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__
     // first four wavefronts hold both
     int hv = 0, hinc = 0, go = 0, tv = 0, tinc = 0;
     if (tid < kRadixBins) {
-        hv = hist[int64_t(tid) * nblk + blk];
         const int32_t* row = offs + int64_t(tid) * nblk;
         go = row[blk];
         tv = total[tid];
+        hv = (blk + 1 < nblk ? row[blk + 1] : tv) - go;
         if constexpr (SEG) {     // the instance's share of the row
             const int before = row[seg.t0];
             tv = (seg.t1 < nblk ? row[seg.t1] : tv) - before;
@@ -975,14 +984,6 @@ int64_t sort_tiles(int64_t n, int n_inst, bool segmented)
     return segmented ? n / kRadixTile + n_inst : radix_blocks(n);
 }
 
-size_t hist_bytes(int64_t n_cap, int n_inst, int key_bits, int64_t tiles)
-{
-    const size_t passes = sizeof(int32_t) * kRadixBins * size_t(tiles);
-    const size_t small =
-        small_sort(n_cap, n_inst, key_bits) ? (sizeof(uint16_t) << key_bits) * size_t(radix_blocks(n_cap)) : 0;
-    return passes > small ? passes : small;
-}
-
 namespace {
 
 // Radix passes of at most this many tiles use the 1024-thread kernels: tree of
@@ -993,8 +994,7 @@ constexpr int kWideTilesMax = 4096;
 
 void scan_table(const Buffers& b, int nblk, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_scan_rows, dim3(kRadixBins), dim3(kRowScanThreads), 0, st, nblk, b.hist, b.hist_scan,
-                       b.scan_part);
+    hipLaunchKernelGGL(k_scan_rows, dim3(kRadixBins), dim3(kRowScanThreads), 0, st, nblk, b.hist, b.scan_part);
 }
 
 }  // namespace
@@ -1022,7 +1022,7 @@ void radix_sort(const Buffers& b, int n, int nblk, bool wide, bool seg, int npas
                                n_dev);
         scan_table(b, nblk, st);
         hipLaunchKernelGGL(scatter, dim3(nblk), dim3(threads), 0, st, n, kin, iin, xin, yin, gin, shift, nblk, b.hist,
-                           b.hist_scan, b.scan_part, out, pass == npass - 1 ? pk : nullptr, b.inst, b.n_inst,
+                           b.scan_part, out, pass == npass - 1 ? pk : nullptr, b.inst, b.n_inst,
                            b.key_shift, n_dev);
         kin = out.k;
         iin = out.idx;
@@ -1043,7 +1043,10 @@ void sort_points(const Buffers& b, int n, const double* x, const double* y, cons
         // 16-bit counts of the wavefronts and a place per leaf in LDS, then (one tile) its records
         const size_t bins = size_t(1) << key_bits;
         const size_t counts_lds = bins * (sizeof(int) + kSmallWaves * sizeof(uint16_t));
-        uint16_t* counts = reinterpret_cast<uint16_t*>(b.hist);
+        // the tiles' counts lie over the temporaries of the passes, 24 bytes a point for 2 bytes a
+        // leaf and tile (at least 4097 points in two tiles and more)
+        static_assert(24 * kRadixTile >= 2 * (sizeof(uint16_t) << kSmallKeyBits), "the counts fit");
+        uint16_t* counts = reinterpret_cast<uint16_t*>(b.ktmp);
         if (nblk == 1) {
             const size_t lds = std::max(counts_lds, size_t(kRadixTile) * (3 * sizeof(double) + 2 * sizeof(uint32_t)));
             hipLaunchKernelGGL(k_small_sort<true>, dim3(1), dim3(kSmallThreads), lds, st, n, nblk, nullptr, x, y, g,
