@@ -341,9 +341,11 @@ k3_spread(Levels3 lv, const double* __restrict__ me, double* __restrict__ mt)
     __shared__ int sbox[64];
     int blk = int(blockIdx.x);
     const int l = level_of3(lv, blk);
-    const int cls = blk & 7, h = 1 << (l - 1), s = h + 2, n = s * s * s, i0 = (blk >> 3) * 64, t = int(threadIdx.x);
+    constexpr int B = fold3(P) ? 1 : 0;      // border
+    const int cls = blk & 7, h = 1 << (l - 1), s = h + 2 * B, n = int(grid3(P, l)), i0 = (blk >> 3) * 64;
+    const int t = int(threadIdx.x);
     if (t < 64) {
-        const int i = i0 + t, x = i % s - 1, y = i / s % s - 1, z = i / (s * s) - 1;
+        const int i = i0 + t, x = i % s - B, y = i / s % s - B, z = i / (s * s) - B;
         const bool in = x >= 0 && y >= 0 && z >= 0 && x < h && y < h && z < h;
         sbox[t] = in ? int((spread3(uint32_t(x)) | spread3(uint32_t(y)) << 1 | spread3(uint32_t(z)) << 2) << 3 | uint32_t(cls))
                      : -1;
@@ -355,7 +357,7 @@ k3_spread(Levels3 lv, const double* __restrict__ me, double* __restrict__ mt)
         sh[i * S + k] = box >= 0 ? src[int64_t(box) * KP + k] : 0.0;
     }
     __syncthreads();
-    double* dst = mt + (grid_off3(l) + cls * int64_t(n)) * KP + i0;
+    double* dst = mt + (grid_off3(P, l) + cls * int64_t(n)) * KP + i0;
     const int i = t & 63;
     if (i0 + i < n)
         for (int k = t >> 6; k < KP; k += kTpb / 64) dst[int64_t(k) * n + i] = sh[i * S + k];
@@ -411,11 +413,15 @@ __device__ __forceinline__ void m2l3(const Levels3& lv, const double* __restrict
     int blk = fmm::xcd_runs(int(blockIdx.x), G, G / fmm::kXcds);
     const int l = level_of3(lv, blk);
     const int cls = blk & 7, cx = cls & 1, cy = (cls >> 1) & 1, cz = cls >> 2;
-    const int h = 1 << (l - 1), n = h * h * h, s = h + 2, n_grid = s * s * s;
+    const int h = 1 << (l - 1), n = h * h * h, s = FOLD ? h + 2 : h, n_grid = int(grid3(P, l));
     const int col = lane & 15, grp = lane >> 4;
-    const double* grid = mt + grid_off3(l) * KP;
-    // the lane's targets as places in the bordered grid, and that plus its term of a step
-    uint32_t box[CG], at[CG];
+    const double* grid = mt + grid_off3(P, l) * KP;
+    // not folded: terms of the last step; the lane's term of it and of the others
+    constexpr int REST = KP - 4 * (NS - 1);
+    const int grp_last = min(grp, REST - 1);
+    // the lane's targets: places in the grid (folded: plus the lane's term of a step), and (not
+    // folded) which of the 27 parents around the target's lie in the cube
+    uint32_t box[CG], at[CG], inside[CG];
     bool valid[CG];
 #pragma unroll
     for (int c = 0; c < CG; ++c) {
@@ -423,7 +429,16 @@ __device__ __forceinline__ void m2l3(const Levels3& lv, const double* __restrict
         valid[c] = t < n;
         const int i = valid[c] ? t : 0, x = i & (h - 1), y = (i >> (l - 1)) & (h - 1), z = i >> (2 * (l - 1));
         box[c] = (spread3(uint32_t(x)) | spread3(uint32_t(y)) << 1 | spread3(uint32_t(z)) << 2) << 3 | uint32_t(cls);
-        at[c] = uint32_t(grp * n_grid + ((z + 1) * s + y + 1) * s + x + 1);
+        if constexpr (FOLD) {
+            at[c] = uint32_t(grp * n_grid + ((z + 1) * s + y + 1) * s + x + 1);
+            inside[c] = 0;
+        } else {
+            at[c] = uint32_t(i);
+            const auto spread = [h](uint32_t m, int k, int by) {       // m at -1, 0, 1 along an axis
+                return (k > 0 ? m : 0u) | m << by | (k < h - 1 ? m << 2 * by : 0u);
+            };
+            inside[c] = spread(spread(spread(1u, x, 1), y, 3), z, 9);
+        }
     }
     f64x4 acc[NT][CG];
 #pragma unroll
@@ -437,8 +452,9 @@ __device__ __forceinline__ void m2l3(const Levels3& lv, const double* __restrict
     // child position and the shift of its parent are the same for all boxes.
     constexpr int NU = FOLD ? 96 : 216;
     struct Operator {
-        const double* a;          // the lane's operator values
+        const double* a;          // the operator (folded: the lane's values)
         const double* src[NV];    // the sources' terms, from the place of the box; null: not in the list
+        uint32_t at[CG];          // not folded: the lane's sources' places
     };
     int turn = 0;
     const auto next = [&](int u, Operator& o) {
@@ -451,13 +467,21 @@ __device__ __forceinline__ void m2l3(const Levels3& lv, const double* __restrict
             if ((turn++ & (W - 1)) == wave) break;
         }
         if (u >= NU) return NU;   // the last operator's values are read once more, not used
-        o.a = op + int64_t(operator3(P, ox, oy, oz)) * (NS * RT * 64) + lane;
+        o.a = op + int64_t(operator3(P, ox, oy, oz)) * operator_size3(P) + (FOLD ? lane : 0);
+        if constexpr (!FOLD) {
+            const int sx = cx - ox, sy = cy - oy, sz = cz - oz, dx = sx >> 1, dy = sy >> 1, dz = sz >> 1;
+            const int bit = (dz + 1) * 9 + (dy + 1) * 3 + dx + 1, to = (dz * h + dy) * h + dx;
+            o.src[0] = grid + int64_t((sx & 1) | (sy & 1) << 1 | (sz & 1) << 2) * KP * n_grid;
+#pragma unroll
+            for (int c = 0; c < CG; ++c) o.at[c] = (inside[c] >> bit) & 1u ? at[c] + uint32_t(to) : uint32_t(n);
+            return u;
+        }
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int sx = cx - ((v & 1) ? -ox : ox), sy = cy - ((v & 2) ? -oy : oy), sz = cz - oz;
             // folded: offsets lie in [c - 3, c + 2], so 3 occurs with one sign only, and 0 once
-            const bool in = !FOLD || (((v & 1) ? ox != 0 && (ox != 3 || cx == 0) : ox != 3 || cx == 1) &&
-                                      ((v & 2) ? oy != 0 && (oy != 3 || cy == 0) : oy != 3 || cy == 1));
+            const bool in = ((v & 1) ? ox != 0 && (ox != 3 || cx == 0) : ox != 3 || cx == 1) &&
+                            ((v & 2) ? oy != 0 && (oy != 3 || cy == 0) : oy != 3 || cy == 1);
             const int pos = (sx & 1) | (sy & 1) << 1 | (sz & 1) << 2;
             o.src[v] = in ? grid + int64_t(pos) * KP * n_grid + ((sz >> 1) * s + (sy >> 1)) * s + (sx >> 1) : nullptr;
         }
@@ -469,9 +493,23 @@ __device__ __forceinline__ void m2l3(const Levels3& lv, const double* __restrict
         double v[CG][NV];
     };
     const auto load = [&](int st, const Operator& o, Step& k) {
+        if constexpr (!FOLD) {
+            // a step's terms past the last are zero times any operator value
+            const bool last = st + 1 == NS;
+            const int term = last ? grp_last : grp;
+            const double* src = o.src[0] + int64_t(4 * st) * n_grid;
+#pragma unroll
+            for (int c = 0; c < CG; ++c) {
+                const double v = src[uint32_t(term * n_grid) + o.at[c]];
+                k.v[c][0] = last && grp >= REST ? 0.0 : v;
+            }
+#pragma unroll
+            for (int i = 0; i < NT; ++i) k.a[i] = o.a[(4 * st + term) * KP + min(16 * i + col, KP - 1)];
+            return;
+        }
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            if (!FOLD || o.src[v]) {
+            if (o.src[v]) {
                 const double* src = o.src[v] + int64_t(4 * st) * n_grid;
 #pragma unroll
                 for (int c = 0; c < CG; ++c) k.v[c][v] = src[at[c]];
@@ -1014,7 +1052,7 @@ hipError_t m2l_p(const Bufs3& b, const Geo3& g, hipStream_t st)
         lv.blk_begin[l - 2] = nm;
         few.blk_begin[l - 2] = nf;
         nf += 8 * int((n + 15) / 16);
-        ns += 8 * int((grid3(l) + 63) / 64);
+        ns += 8 * int((grid3(P, l) + 63) / 64);
         nm += 8 * int((n + 16 * kM2lGroups3 - 1) / (16 * kM2lGroups3));
     }
     sp.blk_begin[g.L - 1] = ns;

@@ -59,15 +59,14 @@ Layout3 layout3(const fmm3d_params* prm)
     ly.leaf_start = take(sizeof(int32_t) * ((size_t(1) << (3 * L)) + 1));
     const size_t coef = off;
     ly.me = take(sizeof(double) * nbox * size_t(stored3(p)));
-    ly.mt = take(sizeof(double) * size_t(grid_off3(L + 1)) * size_t(stored3(p)));
-    ly.le = take(sizeof(double) * nbox * size_t(stored3(p)));
-    ly.op = take(sizeof(double) * size_t(operators3(p)) * size_t(steps3(p)) * size_t(tiles3(p)) * 64);
-    static_assert(stored3(kP3Max) <= 64 * (kP3Max + 1), "the term table fits");
-    ly.term = take(sizeof(int32_t) * 64 * size_t(p + 1));
-    // The size grows with p (a 256-byte row of the term table per degree;
-    // degrees 0 and 1 store the same four terms per box) and is never less than
-    // full sets of coefficients and of derivatives (as rows and as cubes) would
-    // take, what callers of this form budget by.
+    ly.le = ly.me;
+    ly.mt = take(sizeof(double) * size_t(grid_off3(p, L + 1)) * size_t(stored3(p)));
+    ly.op = take(sizeof(double) * size_t(operators3(p)) * size_t(operator_size3(p)));
+    ly.term = take(sizeof(int32_t) * size_t(stored3(p)));
+    // The size is at least what full sets of coefficients and of derivatives (as
+    // rows and as cubes) would take.  The arrays above need 0.43 to 1.0 of that
+    // (degree 0: up to some hundred bytes more), so a buffer made for full sets
+    // holds the plan.
     const size_t S = size_t(2 * p + 1);
     const size_t full = 2 * nbox * size_t(tet3(p + 1)) + size_t(kOffsets3) * (size_t(tet3(2 * p + 1)) + (p > 0 ? S * S * S : 0));
     off = std::max(off, align256(coef + sizeof(double) * full));
@@ -162,16 +161,22 @@ std::vector<int32_t> term_table(int p)
     return t;
 }
 
-// The M2L operators D_(k + n)(o) as the matrix instructions read them: the
-// value of lane l in step st and tile ti has row n = the tile's term l mod 16
-// and column k = the term of lane group l / 16 (zero where either is padding).
+// The M2L operators D_(k + n)(o).  Folded, as the matrix instructions read
+// them: the value of lane l in step st and tile ti has row n = the tile's term
+// l mod 16 and column k = the term of lane group l / 16 (zero where either is
+// padding).  Else by source term k and output term n.
 std::vector<double> operator_table(int p, const std::vector<int32_t>& term)
 {
     const std::vector<double> D = derivative_table(p, fold3(p));
-    const int T2 = tet3(2 * p + 1), NS = steps3(p), RT = tiles3(p);
-    std::vector<double> op(size_t(operators3(p)) * size_t(NS) * size_t(RT) * 64, 0.0);
-    std::vector<int> at(size_t(NS) * size_t(RT) * 64, -1);   // graded position of k + n, the same for every offset
-    for (int cl = 0; cl < classes3(p); ++cl)
+    const int T2 = tet3(2 * p + 1), NS = steps3(p), RT = tiles3(p), KP = stored3(p);
+    std::vector<double> op(size_t(operators3(p)) * size_t(operator_size3(p)), 0.0);
+    std::vector<int> at(size_t(operator_size3(p)), -1);      // graded position of k + n, the same for every offset
+    const auto sum = [](int n, int k) {
+        return pos3((n & 255) + (k & 255), ((n >> 8) & 255) + ((k >> 8) & 255), (n >> 16) + (k >> 16));
+    };
+    for (int k = 0; !fold3(p) && k < KP; ++k)
+        for (int n = 0; n < KP; ++n) at[size_t(k * KP + n)] = sum(term[size_t(n)], term[size_t(k)]);
+    for (int cl = 0; fold3(p) && cl < classes3(p); ++cl)
         for (int i = 0; i < class_tiles3(p, cl); ++i)
             for (int st = 0; st < NS; ++st)
                 for (int l = 0; l < 64; ++l) {
@@ -179,8 +184,7 @@ std::vector<double> operator_table(int p, const std::vector<int32_t>& term)
                     if (row >= class_size3(p, cl)) continue;
                     const int n = term[size_t(class_base3(p, cl) + row)], k = term[size_t(4 * st + l / 16)];
                     if (n < 0 || k < 0) continue;
-                    at[(size_t(st) * size_t(RT) + size_t(tile_base3(p, cl) + i)) * 64 + size_t(l)] =
-                        pos3((n & 255) + (k & 255), ((n >> 8) & 255) + ((k >> 8) & 255), (n >> 16) + (k >> 16));
+                    at[(size_t(st) * size_t(RT) + size_t(tile_base3(p, cl) + i)) * 64 + size_t(l)] = sum(n, k);
                 }
     const int lo = fold3(p) ? 0 : -3;
     for (int oz = -3; oz <= 3; ++oz)

@@ -9,10 +9,10 @@
 // are folded into these, those of a local set follow from these, in either
 // case within one degree, so nothing but rounding changes.
 //
-// Kept terms are stored by class, the parities of (a, b) (four classes where
-// the M2L folds reflections, fold3(p); else one class), each class padded to
-// a multiple of 4 with zeros: the M2L's matrix instructions take four source
-// terms of one class.  Graded order (degree, then s = b + c, then c) puts
+// Kept terms are stored by class, the parities of (a, b): four classes where
+// the M2L folds reflections (fold3(p)), each padded to a multiple of 4 with
+// zeros, since the M2L's matrix instructions take four source terms of one
+// class; else one class, not padded.  Graded order (degree, then s = b + c, then c) puts
 // (a, b, c) of a full set at tet(a + b + c) + tri(b + c) + c with tet(d) =
 // d (d+1) (d+2) / 6 and tri(s) = s (s+1) / 2.
 #pragma once
@@ -48,7 +48,7 @@ __host__ __device__ constexpr int off3_index(int ox, int oy, int oz) { return ((
 __host__ __device__ constexpr bool fold3(int p) { return p >= 5; }
 __host__ __device__ constexpr int classes3(int p) { return fold3(p) ? 4 : 1; }
 __host__ __device__ constexpr int class3(int p, int a, int b) { return fold3(p) ? (a & 1) | ((b & 1) << 1) : 0; }
-// kept terms of a class, and that padded
+// kept terms of a class, and stored ones
 __host__ __device__ constexpr int class_terms3(int p, int cl)
 {
     int n = 0;
@@ -57,7 +57,10 @@ __host__ __device__ constexpr int class_terms3(int p, int cl)
             for (int b = 0; a + b + c <= p; ++b) n += class3(p, a, b) == cl ? 1 : 0;
     return n;
 }
-__host__ __device__ constexpr int class_size3(int p, int cl) { return (class_terms3(p, cl) + 3) / 4 * 4; }
+__host__ __device__ constexpr int class_size3(int p, int cl)
+{
+    return fold3(p) ? (class_terms3(p, cl) + 3) / 4 * 4 : class_terms3(p, cl);
+}
 __host__ __device__ constexpr int class_base3(int p, int cl)
 {
     int n = 0;
@@ -69,7 +72,7 @@ __host__ __device__ constexpr int stored3(int p) { return class_base3(p, classes
 
 // M2L matrix instructions: steps of four source terms, 16-row tiles of output
 // terms.
-__host__ __device__ constexpr int steps3(int p) { return stored3(p) / 4; }
+__host__ __device__ constexpr int steps3(int p) { return (stored3(p) + 3) / 4; }
 __host__ __device__ constexpr int class_tiles3(int p, int cl) { return (class_size3(p, cl) + 15) / 16; }
 __host__ __device__ constexpr int tile_base3(int p, int cl)
 {
@@ -85,20 +88,30 @@ __host__ __device__ constexpr int operator3(int p, int ox, int oy, int oz)
     return fold3(p) ? ((oz + 3) * 4 + oy) * 4 + ox : off3_index(ox, oy, oz);
 }
 
+// doubles of one operator: folded, a lane's value of every matrix instruction
+// (steps, tiles, 64); else the stored terms' square, [source][output]
+__host__ __device__ constexpr int operator_size3(int p)
+{
+    return fold3(p) ? steps3(p) * tiles3(p) * 64 : stored3(p) * stored3(p);
+}
+
 // M2L sources of level l (l >= 2): the boxes of one child position form the
 // grid of their parents, 2^(l-1) a side.  The sources of a box lie under its
-// parent and the parents touching that one, so with a border of one they are
-// all found at a fixed distance, zero outside the cube.
-__host__ __device__ constexpr int64_t grid3(int l)
+// parent and the parents touching that one: at a fixed distance, zero outside
+// the cube.  Folded: with a border of one, so that they are found there.  Else
+// one zero box behind the grid and a lane turned to it where its source is
+// outside, which keeps the few terms of these degrees within the workspace of
+// two full sets (a border adds 7 to 12 % at depth 7, six times the boxes at 2).
+__host__ __device__ constexpr int64_t grid3(int p, int l)
 {
-    const int64_t s = (int64_t(1) << (l - 1)) + 2;
-    return s * s * s;
+    const int64_t h = int64_t(1) << (l - 1), s = h + 2;
+    return fold3(p) ? s * s * s : h * h * h + 1;
 }
 // first source double of level l, in boxes (times stored3(p))
-__host__ __device__ constexpr int64_t grid_off3(int l)
+__host__ __device__ constexpr int64_t grid_off3(int p, int l)
 {
     int64_t n = 0;
-    for (int k = 2; k < l; ++k) n += 8 * grid3(k);
+    for (int k = 2; k < l; ++k) n += 8 * grid3(p, k);
     return n;
 }
 
@@ -117,10 +130,10 @@ struct Bufs3 {
     int32_t* leaf_start;        // [8^L + 1] sorted range of every leaf; the last entry counts the inside ones
     double* me;                 // [boxes of levels 0..L][stored3(p)] scaled moments
     double* mt;                 // levels 2..L: the moments again as the M2L reads them, [child position][stored3(p)]
-                                // [parents of the level above, x fastest, with a border of zeros]
-    double* le;                 // [boxes of levels 0..L][stored3(p)] scaled local coefficients
-    double* op;                 // [operators3(p)][steps3(p)][tiles3(p)][64] M2L operators, a lane's value of each
-                                // matrix instruction
+                                // [parents of the level above, x fastest, and zeros: grid3]
+    double* le;                 // [boxes of levels 0..L][stored3(p)] scaled local coefficients (over me: the M2L
+                                // reads mt alone)
+    double* op;                 // [operators3(p)][operator_size3(p)] M2L operators
     int32_t* term;              // [stored3(p)] a | b << 8 | c << 16 of every stored position, -1: padding
     unsigned long long* nbad;   // particles outside the cube or NaN
 };

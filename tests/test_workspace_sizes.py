@@ -31,3 +31,22 @@ import paper_0905_2637_amd as fm
 def test_no_larger(n, depth, held, kw):
     prm = fm.make_params(n, 0.3 / 2 ** depth, 12, depth, fp32_fine_levels=min(2, depth - 1), **kw)
     assert fm.workspace_size(prm) <= held
+
+
+# bytes that 3D plans of 1,000 particles asked for with full sets of coefficients, degrees 0 to 9
+HELD_3D = {
+    0: [84224, 183552, 520960, 1253632, 2535424, 4519424, 7360512, 11210496, 16225280, 22556160],
+    2: [85504, 188416, 532480, 1276928, 2575616, 4584192, 7457536, 11348992, 16415488, 22809856],
+    5: [814336, 2711296, 6643456, 13368064, 23636992, 38203904, 57821696, 83241728, 115218944, 154504192],
+    7: [46820608, 161963776, 392388352, 776600320, 1353100288, 2160390656, 3236973056, 4621347584, 6352017920,
+        8467483648],
+}
+
+
+@pytest.mark.parametrize("depth", sorted(HELD_3D))
+@pytest.mark.parametrize("p", range(10))
+def test_no_larger_3d(depth, p):
+    import ctypes as C
+    prm, out = fm.Fmm3dParams(1000, p, depth, 0.0, 0.0, 0.0, 1.0), C.c_size_t(0)
+    assert fm.load().fmm3d_workspace_size(C.byref(prm), C.byref(out)) == fm.FMM_OK
+    assert out.value <= HELD_3D[depth][p]
