@@ -204,8 +204,6 @@ struct fmm3d_plan_s {
     fmm3d_params prm;
     Bufs3 buf;
     Geo3 geo;
-    std::vector<double> op_host;     // sources of the table uploads, kept until the plan ends
-    std::vector<int32_t> term_host;
     int64_t last_n = 0;
 };
 
@@ -266,18 +264,21 @@ fmm_status fmm3d_plan(const fmm3d_params* prm, void* d_workspace, size_t bytes, 
     g.L = prm->depth;
     g.p = prm->p;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    std::vector<int32_t> term;
+    std::vector<double> op;
     try {
-        pl->term_host = term_table(prm->p);
-        pl->op_host = operator_table(prm->p, pl->term_host);
+        term = term_table(prm->p);
+        op = operator_table(prm->p, term);
     } catch (...) {
         delete pl;
         return FMM_E_NOMEM;
     }
-    if (hipMemcpyAsync(b.op, pl->op_host.data(), pl->op_host.size() * sizeof(double), hipMemcpyHostToDevice, st) !=
-            hipSuccess ||
-        hipMemcpyAsync(b.term, pl->term_host.data(), pl->term_host.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                       st) != hipSuccess ||
-        launch3_clear(b, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
+    hipError_t e = hipMemcpyAsync(b.op, op.data(), op.size() * sizeof(double), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(b.term, term.data(), term.size() * sizeof(int32_t), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = launch3_clear(b, st);
+    // the host tables go out of scope, also after a failure
+    if (hipStreamSynchronize(st) != hipSuccess || e != hipSuccess) {
         delete pl;
         return FMM_E_DEVICE;
     }
