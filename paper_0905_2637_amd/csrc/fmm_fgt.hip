@@ -204,13 +204,18 @@ k_h2t_axis(int L, int nc, int axis, const double* __restrict__ in, const double*
 }
 
 // T2P: one particle (or target point) per thread in sorted order, G to its
-// input position; v is cleared.  The points of a wavefront lie in few boxes
-// where boxes hold many: up to kT2pBoxes of them, the coefficients of each
-// come through scalar loads, shared by all lanes (every lane evaluates every
-// box of its wavefront and keeps its own); otherwise each lane gathers those
-// of its own box.  Bound by the vector loads of the coefficients when
-// gathered: 37 us on 2^20 particles in 4,096 boxes (P = 12), 24 us by boxes.
-constexpr int kT2pBoxes = 4;
+// input position; v is cleared.  Where the points of a wavefront lie in at most
+// kT2pBoxes boxes, the coefficients of each come through scalar loads, shared
+// by all lanes (every lane evaluates every box of its wavefront and keeps its
+// own); otherwise each lane gathers those of its own box.  Bound by the vector
+// loads of the coefficients when gathered; the scalar ones are a chain of
+// latencies, which pays for one box only, and from four wavefronts a SIMD on.
+// Whole evaluations gathered / one box shared / up to four, us: 2^20 particles,
+// 4,096 boxes 154 / 144 / 148 (p = 12), 194 / 166 / 183 (16); 2^18, 256 boxes
+// 73 / 69 / 78 (16); 2^17, 256 boxes 57 / 59 / 69 (16); 2^18, 4,096 boxes
+// 112 / 112 / 125 (16).
+constexpr int kT2pBoxes = 1;
+constexpr int kT2pSharedMin = 1 << 18;
 
 template <int P, typename Coef>
 __device__ __forceinline__ double taylor2(const Coef* __restrict__ b, double u1, double u2)
@@ -244,7 +249,7 @@ k_t2p(int n, int L, const Inst* __restrict__ inst, const uint32_t* __restrict__ 
     const uint32_t prev = uint32_t(__shfl_up(int(m), 1, 64));
     const int boxes = 1 + __popcll(__ballot(__lane_id() > 0 && m != prev));
     double acc = 0.0;
-    if (boxes <= kT2pBoxes) {
+    if (n >= kT2pSharedMin && boxes <= kT2pBoxes) {
         uint64_t todo = __ballot(true);
         while (todo) {
             const uint32_t mu = uint32_t(__builtin_amdgcn_readlane(int(m), __ffsll((unsigned long long)todo) - 1));

@@ -82,3 +82,22 @@ def test_points(p, L, n, m):
     Go, nbad = oracle.fgt_at(x, y, q, sigma, p, L, _range(sigma, L), tx, ty)
     assert nbad == 0
     _check(G, Go)
+
+
+@pytest.mark.parametrize("p", [8, 12, 16])
+def test_shared_coefficients(p):
+    """From 2^18 points on, wavefronts within one box read its coefficients
+    through scalar loads: the same values as for a few points, which never do,
+    bit for bit."""
+    import torch
+    import paper_0905_2637_amd as fm
+    n, L = (1 << 18) + 77, 4
+    dev = _dev(*workloads.uniform_square(n, 985))
+    plan = fm.Plan(n, 1.0 / 2 ** L, p, L, kernel="gauss-transform", m_max=n)
+    all_at = plan.evaluate(*dev)[0].clone()
+    points = [t[:5000].contiguous() for t in dev[:2]]
+    few = plan.evaluate_at(*dev, *points)[0].clone()
+    at = plan.evaluate_at(*dev, *dev[:2])[0]
+    torch.cuda.synchronize()
+    assert torch.equal(all_at[:5000], few) and torch.equal(all_at, at)
+    plan.close()
