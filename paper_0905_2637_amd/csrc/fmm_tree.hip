@@ -899,11 +899,16 @@ __device__ __forceinline__ int64_t leaf_entry(uint32_t k, const Inst* __restrict
 // A workgroup takes kBoundsRounds x 256 consecutive positions, 256 per round
 // (coalesced); all its key loads are issued before any range is written,
 // and a single-instance plan reads its instance record once.
-// A gap of kBoundsGap empty leaves and more is filled by the whole wavefront:
+// A gap of more than kBoundsGap empty leaves is filled by the whole wavefront:
 // one thread's loop over a clustered tree's gaps took longer than all the key
-// loads (2^22 particles of 16 clusters, 2^18 leaves: 53 us, 14 here).
+// loads (2^22 particles of 16 clusters, 2^18 leaves: 53 us, 14 here); below, a
+// round of the wavefront for each of its gaps costs more than the loops side by
+// side.  Tree stage with the line at 2 / 8 / 32 / never, us: 2^20 of 16
+// clusters, 2^20 leaves 151 / 126 / 122 / 701; uniform, 2^20 leaves: 2^20
+// particles 102 / 94 / 94 / 94, 2^18 123 / 90 / 85 / 86, 2^16 142 / 124 / 98 /
+// 117, 4,096 249 / 249 / 256 / 819.
 constexpr int kBoundsRounds = 16;
-constexpr int kBoundsGap = 8;
+constexpr int kBoundsGap = 32;
 
 __global__ void __launch_bounds__(256)
 k_bounds(int n, int64_t entries, const uint32_t* __restrict__ ks, const Inst* __restrict__ inst, int n_inst,

@@ -74,3 +74,34 @@ def test_instances_apart_on_many_tiles():
         else:
             assert np.all(ls_all[seg:seg + ent] == off)
         off, seg = off + c, seg + ent
+
+
+@pytest.mark.parametrize("L", [7, 9])
+def test_runs_of_empty_leaves(L):
+    """Runs around the length from which a wavefront fills them together, long
+    ones, and none, side by side and at both ends."""
+    import torch
+    import paper_0905_2637_amd as fm
+    rng = np.random.default_rng(996 + L)
+    runs = [0, 1, 7, 8, 9, 30, 31, 32, 33, 34, 63, 64, 65, 66, 127, 128, 129, 300, 2000]
+    leaf, at = [], 40
+    while True:
+        at += 1 + int(rng.choice(runs))
+        if at >= 4 ** L - 200:
+            break
+        leaf += [at] * int(rng.integers(1, 3))
+    k = np.array(leaf, dtype=np.uint64)
+    a, b = np.zeros(len(k)), np.zeros(len(k))
+    for bit in range(L):
+        a += ((k >> np.uint64(2 * bit)) & np.uint64(1)) * 2.0 ** bit
+        b += ((k >> np.uint64(2 * bit + 1)) & np.uint64(1)) * 2.0 ** bit
+    order = rng.permutation(len(k))
+    x, y = (((c + 0.1 + 0.8 * rng.random(len(k))) / 2 ** L)[order] for c in (a, b))
+    plan = fm.Plan(300000, 1e-4, 8, L)
+    plan.evaluate(*_dev(x, y, np.ones(len(x))))
+    torch.cuda.synchronize()
+    key, perm, ls, nbad = oracle.tree(x, y, L)
+    assert nbad == 0 and len(np.unique(np.diff(np.unique(key)))) > 10
+    assert np.array_equal(plan.dump(fm.DUMP_KEYS), key) and np.array_equal(plan.dump(fm.DUMP_PERM), perm)
+    assert np.array_equal(plan.dump(fm.DUMP_LEAF_START), ls)
+    plan.close()
