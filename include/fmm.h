@@ -403,8 +403,9 @@ const char* fmm_status_string(fmm_status s);
  * the 26 leaves touching it, evaluated directly; interaction list = the up
  * to 189 boxes of the same level whose parents touch the box's parent but
  * which do not touch the box.  Far field through Cartesian Taylor
- * expansions of total degree <= p ((p+1)(p+2)(p+3)/6 terms per box): P2M,
- * M2M, M2L, L2L, L2P.  FP64 throughout.  The 3D vortex velocity is the curl
+ * expansions of total degree <= p: P2M, M2M, M2L, L2L, L2P.  1/r is harmonic,
+ * so the (p+1)^2 terms of degree <= 1 in z stand for all
+ * (p+1)(p+2)(p+3)/6.  FP64 throughout.  The 3D vortex velocity is the curl
  * of three such potentials (one per vorticity component); that combination
  * is left to the caller.
  *
@@ -424,7 +425,10 @@ typedef struct {
     double width;       /* its side, > 0 */
 } fmm3d_params;
 
-/* Bytes of device workspace a plan with these parameters needs.  Host only.
+/* Bytes of device workspace a plan with these parameters needs: about 76 per
+ * particle, and what two full sets of (p+1)(p+2)(p+3)/6 doubles per box and the
+ * derivatives of 1/r to degree 2p at 343 offsets take (a size that callers may
+ * hold; the arrays themselves need 0.43 to 1.0 of the latter).  Host only.
  * Errors: FMM_E_ARG (NULL, negative or non-finite values), FMM_E_UNSUPPORTED
  * (p > 9 or depth > 7). */
 fmm_status fmm3d_workspace_size(const fmm3d_params* prm, size_t* bytes);

@@ -14,8 +14,9 @@
 //            t_i = +1 / -1 as the child centre lies above / below the parent's
 //   L2P      phi(x) = (1/w) sum_n Ls_n u^n / n!,  d phi / dx_i = (1/w^2) sum_n Ls_n u^(n-e_i) / (n-e_i)!,
 //            u = (x - c) / w
-// The scaling makes the M2L data level-independent: one table of D_m at the
-// 316 integer offsets of the interaction lists.
+// The scaling makes the M2L data level-independent: one operator D_(k+n) per
+// integer offset of the interaction lists, from degree 5 on for non-negative x
+// and y offsets only (the M2L reaches the others by reflection).
 //
 // Only the terms of degree <= 1 in z are kept: see fmm3d_internal.h.
 //
@@ -913,7 +914,11 @@ __device__ __forceinline__ void chunk3(double4 s, int t0, int t, int part, int n
 // wavefronts per leaf, each a quarter of the source chunks (few leaves).
 // Targets in chunks of 64, laid out as R per lane (near3) for the most lanes
 // on real pairs; the sources of the near leaves staged in LDS, 256 at a time,
-// leaf after leaf without gaps.  Bound by the vector units: 2^20 charges,
+// leaf after leaf without gaps.  Held to 128 registers (four wavefronts per
+// SIMD) it spills 3 to 11 of them from p = 1 on, 15 at p = 7, outside the
+// pair loop; three wavefronts without spills are slower (p = 6: 1,500 us a
+// whole evaluation instead of 1,485; 2^21 charges, depth 6, p = 2: 1,913 and
+// 1,826).  Bound by the vector units: 2^20 charges,
 // depth 5 (about 32 per leaf, 864 near sources), p = 6: 861 us, against 2,510
 // us with one target per lane (half the lanes idle at 32 per leaf) and a
 // library square root and division per pair.

@@ -250,14 +250,18 @@ __device__ __forceinline__ void m2l_items_block(T* bx, T* by, const cplx<T>* __r
 // product there too.  The other children mirror the offsets (x for child x =
 // 1, y for y = 1; s is the product of the mirrors' signs).  20 multiply-adds
 // per output and input term and 144 additions per input term, against 52 and
-// 48 for the pairs above.  The FP32 levels keep the pairs: their sums would
-// round differently.  So does FP64 past P = 24: the operands of a class and
-// 2 P accumulators do not fit the registers (248 us by pairs, 490 by classes
-// at P = 32, 1M particles).  M2L stage, pairs -> classes: 32 -> 29 us (P = 8),
+// 48 for the pairs above.  The FP32 levels keep the pairs by choice: by
+// classes their sums would round differently, and the mixed form's results
+// stay as they are.  FP64 keeps them past P = 24, where the operands of a
+// class and 2 P accumulators do not fit the registers (248 us by pairs, 490 by
+// classes at P = 32, 1M particles; at P = 24 14 registers spill, and the
+// classes are the faster all the same).  M2L stage, pairs -> classes: 32 -> 29 us (P = 8),
 // 50 -> 43 (12), 86.5 -> 72 (17), 103 -> 78 (20), 139 -> 119 (24) at 1M
 // particles, depth 8; 1175 -> 778 at 16M, depth 10, P = 20; 39 -> 30 at 200k,
-// depth 6, P = 17.  Bound by FP64 issue at two wavefronts per SIMD; one input
-// term at a time (three wavefronts fit) reads each datum twice as often for
+// depth 6, P = 17.  At two wavefronts per SIMD it fills a quarter of the FP64
+// issue cycles at 1M particles (18 of 71 us) and half at 64M (1.55 of 3.1 ms);
+// the rest is waits: scalar loads of the data, one residue ahead, and the
+// stage.  One input term at a time (three wavefronts fit) reads each datum twice as often for
 // its product: 81 us at P = 17, 267 at 24.  Data residue by residue instead
 // of in order of n (below): 74 -> 72 at P = 17, 134 -> 119 at 24, 824 -> 778
 // at 16M.
@@ -485,8 +489,9 @@ __device__ __forceinline__ void m2l_for_chunks(F f, std::integer_sequence<int, C
     (f(std::integral_constant<int, C>{}), ...);
 }
 
-// gridDim.y = G in {1, 2, 3}: workgroup row g takes every G-th work item
-// (the matrix-core kernel: every G-th member of the interaction list) and
+// gridDim.y = G in {1, 2, 3}: workgroup row g takes the classes of
+// m2l_class_mask (FP64, P <= 24), every G-th work item (FP32 and P = 32) or
+// every G-th member of the interaction list (the matrix-core kernel), and
 // writes its partial sum to out[g] (out[0] = le).
 struct M2LOut {
     cd* out[3];

@@ -654,10 +654,10 @@ __device__ __forceinline__ void quad_pairs(const Src64* qsh, int lane, int w, co
 
 // WAVES wavefronts per workgroup, one leaf each (four: one quad); the work
 // table gives every instance ceil(4^L / WAVES) workgroups.  The occupancy is
-// set where the compiler would spend registers past it: mixed 83 instead of 66
-// (2^22 clustered particles 1,341 -> 1,250 us, with the row variants of
-// leaf_near_far; 512 instances of 64 per leaf 2,782 -> 2,390 us), and
-// Lennard-Jones 105 (144 -> 133 us with five wavefronts per SIMD).
+// set where the compiler would spend registers past it: mixed 83 instead of 71
+// (seven wavefronts per SIMD; 2^22 clustered particles 1,341 -> 1,236 us, with
+// the row variants of leaf_near_far; 512 instances of 64 per leaf 2,782 -> 2,303
+// us), and Lennard-Jones 105 (144 -> 133 us with five wavefronts per SIMD).
 template <int P, bool MIXED, int WAVES, int KER>
 __global__ void __launch_bounds__(64 * WAVES, MIXED ? 7 : KER == kNearLJ ? 5 : 0)
 k_p2p_l2p(Work wk, int n_inst, const Inst* __restrict__ inst, const int32_t* __restrict__ leaf_start_all,

@@ -41,6 +41,12 @@ struct SchedCfg {
 constexpr int kMaxLaunches = 16;
 // Interaction-list wavefront split: FP64 levels of an instance with fewer
 // than this many split-level tiles use three wavefronts per list, else two.
+// This line and the deepest split level were set for the M2L by pairs.  By
+// classes, unsplit / split up to level 8, us: depth 4 (3 tiles with the levels
+// above) 40 / 24 (P = 17), 64 / 40 (24); depth 6 (22 tiles) 46 / 30; depth 7
+// (86) 46 / 35; but depth 8 (342) 58 / 71 (17), 69 / 79 (20), 104 / 118 (24);
+// depth 9 174 / 192; depth 10 585 / 602 (17): two rows stage all sources twice
+// and no longer pay.  The autotuner finds that; the default keeps the split.
 constexpr int kM2LFewTiles = 256;
 
 __host__ __device__ inline int sched_split_level(int L, int split_max)
