@@ -236,6 +236,7 @@ fmm_status fmm3d_plan(const fmm3d_params* prm, void* d_workspace, size_t bytes, 
     Bufs3& b = pl->buf;
     b.sort = fmm::Buffers{};
     b.sort.hist = static_cast<int32_t*>(at(ly.hist));
+    b.sort.hist_scan = b.sort.hist;
     b.sort.scan_part = static_cast<int32_t*>(at(ly.scan_part));
     b.sort.ktmp = static_cast<uint32_t*>(at(ly.ktmp));
     b.sort.itmp = static_cast<uint32_t*>(at(ly.itmp));

@@ -198,7 +198,7 @@ fmm_status batch_shape(const fmm_params* prm, Shape& sh, int64_t& max_leaves)
 }
 
 struct Layout {
-    size_t inst, tables, bad_blk, bbox, leaf_start, hist;
+    size_t inst, tables, bad_blk, bbox, leaf_start, hist, hist_scan;
     size_t key, ksorted, perm, xs, ys, gs, ktmp, itmp, xt, yt, gt, pk, blk_tab, me, le, le_part[2];
     size_t tkey, tks, tperm, txs, tys, tleaf_start, tbad;
     size_t fgt_a, fgt_b, fgt_h;
@@ -212,7 +212,8 @@ Layout make_layout(const Shape& sh, int P, bool mixed)
     const size_t n = size_t(std::max<int64_t>(sh.n_cap, 1));
     const size_t m = size_t(sh.m_cap);
     const size_t nm = std::max(n, m);   // the radix temporaries serve both point sets
-    const size_t nblk = size_t(sort_tiles(int64_t(nm), sh.n_inst, seg_sort(sh.n_cap, sh.n_inst, 2 * sh.Lmax)));
+    const bool apart = seg_sort(sh.n_cap, sh.n_inst, 2 * sh.Lmax);
+    const size_t nblk = size_t(sort_tiles(int64_t(nm), sh.n_inst, apart));
     Layout ly{};
     size_t off = 0;
     auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes); return o; };
@@ -222,6 +223,7 @@ Layout make_layout(const Shape& sh, int P, bool mixed)
     ly.bbox = take(sizeof(double) * 8 * kBBoxBlocks);
     ly.leaf_start = take(sizeof(int32_t) * size_t(sh.leaf_entries));
     ly.hist = take(sizeof(int32_t) * kHistDigits * nblk);
+    ly.hist_scan = apart ? ly.hist : take(sizeof(int32_t) * kHistDigits * nblk);
     ly.key = take(sizeof(uint32_t) * n);
     ly.ksorted = take(sizeof(uint32_t) * n);
     ly.perm = take(sizeof(uint32_t) * n);
@@ -645,6 +647,7 @@ fmm_status make_plan(const fmm_params* prm, Shape&& sh, bool batch, void* d_work
     b.bbox = reinterpret_cast<double*>(base + ly.bbox);
     b.leaf_start = reinterpret_cast<int32_t*>(base + ly.leaf_start);
     b.hist = reinterpret_cast<int32_t*>(base + ly.hist);
+    b.hist_scan = reinterpret_cast<int32_t*>(base + ly.hist_scan);
     b.scan_part = reinterpret_cast<int32_t*>(b.bbox);   // reduced before the sort
     b.key = reinterpret_cast<uint32_t*>(base + ly.key);
     b.ksorted = reinterpret_cast<uint32_t*>(base + ly.ksorted);

@@ -159,7 +159,8 @@ struct Buffers {
     int32_t* leaf_start;   // [sum (4^L_i + 1)] sorted ranges of every leaf of every instance
     bool seg_sort;         // the instances are sorted apart, by the leaf bits only
     bool small_sort;       // the particles (and target points) sort in one pass over the whole key
-    int32_t* hist;         // [256 * sort_tiles] digit-major tile histograms, then their rows' exclusive scans
+    int32_t* hist;         // [256 * sort_tiles] digit-major tile histograms
+    int32_t* hist_scan;    // [256 * sort_tiles] exclusive scans of its rows (sorts apart and the 3D form: in place)
     int32_t* scan_part;    // [256] the rows' totals (2D plans: over bbox)
     uint32_t* key;         // [n_max] instance and leaf key per input particle
     uint32_t* ksorted;     // [n_max] sorted keys

@@ -7,17 +7,21 @@
 // at any level form one contiguous range of the key-sorted particle array.
 //
 // Sort: least-significant-digit radix sort with 8-bit digits, ceil(2L/8)
-// passes.  Each pass is a per-tile digit histogram, an exclusive scan of the
-// digit-major histogram table, and a stable scatter in which every wavefront
+// passes; single plans of few particles and leaves take one counting pass over
+// the whole key instead (small sorts, below).  Each digit pass is a per-tile
+// digit histogram, an exclusive scan of the digit-major histogram table, and a
+// stable scatter in which every wavefront
 // ranks its 64 keys by digit with 8 ballots (lanes sharing a digit are found
 // by intersecting the ballots of the digit's bits).  Every pass is stable, so
 // the final permutation is the unique one with ties in input order, and no
 // global atomics are involved: the result is bit-for-bit reproducible.
 //
-// Several instances sort together: the key of a particle of instance i is
-// (i << 2 L_max) | (leaf key at depth L_i << 2 (L_max - L_i)), which orders
-// instances first and leaves within each instance, so every instance's
-// particles end up contiguous and in their own leaf order.
+// Several instances: the key of a particle of instance i is (i << 2 L_max) |
+// (leaf key at depth L_i << 2 (L_max - L_i)), which orders instances first and
+// leaves within each instance, so every instance's particles end up contiguous
+// and in their own leaf order.  The input holds the instances one after the
+// other, so plans with room for enough particles an instance sort them apart,
+// by the leaf bits only (tile_of); the others sort together by the whole key.
 //
 // The particle record (key, input index, x, y, gamma) travels with the sort,
 // so every pass reads and writes whole streams (the scatter writes runs of
@@ -138,26 +142,27 @@ __device__ __forceinline__ int wave_incl_scan(int v)
 }
 
 // Histogram table of a radix pass, digit-major [256][nblk]: one workgroup per
-// digit scans its row in place (exclusive) and writes the digit's total; the
-// scatter turns the 256 totals into the digits' starts itself, and takes a
-// tile's count as the difference to the next entry.  A wavefront takes a run of
-// the row, 64 tiles a round, four rounds' loads at once.  Latency-bound: 4.7 us
-// a pass on 256 tiles and 14 us on 16,384, against 9.5 and 30 us for a
-// two-level scan of the whole table by two kernels.
+// digit scans its row into out (exclusive; out may be the table itself) and
+// writes the digit's total; the scatter turns the 256 totals into the digits'
+// starts itself.  A wavefront takes a run of the row, 64 tiles a round, four
+// rounds' loads at once.  Latency-bound: 4.7 us a pass on 256 tiles and 14 us
+// on 16,384, against 9.5 and 30 us for a two-level scan of the whole table by
+// two kernels.
 constexpr int kRowScanThreads = 1024;
 constexpr int kRowScanWaves = kRowScanThreads / 64;
 
 __global__ void __launch_bounds__(kRowScanThreads)
-k_scan_rows(int nblk, int32_t* __restrict__ table, int32_t* __restrict__ total)
+k_scan_rows(int nblk, const int32_t* in, int32_t* out, int32_t* __restrict__ total)
 {
     __shared__ int wsum[kRowScanWaves];
     const int lane = __lane_id(), w = threadIdx.x >> 6;
     const int run_tiles = ((nblk + kRowScanThreads - 1) / kRowScanThreads) * 64;
     const int b0 = min(nblk, w * run_tiles), b1 = min(nblk, b0 + run_tiles);
-    int32_t* row = table + int64_t(blockIdx.x) * nblk;
+    const int32_t* src = in + int64_t(blockIdx.x) * nblk;
+    int32_t* dst = out + int64_t(blockIdx.x) * nblk;
     int s = 0;
 #pragma unroll 8
-    for (int b = b0 + lane; b < b1; b += 64) s += row[b];
+    for (int b = b0 + lane; b < b1; b += 64) s += src[b];
     s = wave_incl_scan(s);
     if (lane == 63) wsum[w] = s;
     __syncthreads();
@@ -172,14 +177,14 @@ k_scan_rows(int nblk, int32_t* __restrict__ table, int32_t* __restrict__ total)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int b = c + 64 * r + lane;
-            v[r] = b < b1 ? row[b] : 0;
+            v[r] = b < b1 ? src[b] : 0;
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             if (c + 64 * r >= b1) break;
             const int b = c + 64 * r + lane;
             const int inc = wave_incl_scan(v[r]);
-            if (b < b1) row[b] = run + inc - v[r];
+            if (b < b1) dst[b] = run + inc - v[r];
             run += __builtin_amdgcn_readlane(inc, 63);
         }
     }
@@ -214,8 +219,12 @@ __device__ __forceinline__ int particle_inst(const Inst* __restrict__ inst, int 
 // as many as it needs; a tile's records go to places of its own instance.
 // 512 instances of 2,048 to 65,536 particles, 10 leaf bits: two passes
 // instead of three and no search for a particle's instance, tree 760 -> 529 us.
-// Small instances would leave the tiles mostly empty; they sort by the whole
-// key.
+// Apart / by the whole key, evaluations (mixed, P = 8) in us: 64 instances of
+// 16,384 445 / 467, 512 of 16,384 2,862 / 3,186; of 6,144 167 / 190 and 681 /
+// 787, of 512 114 / 139 and 177 / 195 (mostly empty tiles, and the faster all
+// the same).  The line is drawn for the workspace: a tile an instance more
+// means a histogram row entry for each digit more, and plans need no more than
+// the passes over the whole key did.
 constexpr int kSegMinPer = 2 * kRadixTile;
 
 __device__ __forceinline__ int64_t seg_tile(const Inst* __restrict__ inst, int q)
@@ -394,7 +403,11 @@ struct Records {
 // threads write consecutive addresses of each digit's run (offs[d * nblk +
 // block] is where the tile's run starts among digit d, total[d] the count of
 // digit d; where segmented, both less those of the instances before): whole
-// cache lines instead of scattered 8-byte writes.
+// cache lines instead of scattered 8-byte writes.  hist == nullptr: the table
+// was scanned in place, and a tile's count is the difference to the next entry
+// (sorts apart and the 3D form have no room for a second table within the
+// workspace that they always had; three passes of 16M records take 801 us with
+// it, 803 to 819 without).
 // iin == nullptr means the identity (first pass).  pk != nullptr (last pass,
 // mixed precision) also writes the FP32 leaf-relative record
 // (x - c, y - c) / w_L, gamma of the leaf centre c.
@@ -402,8 +415,8 @@ template <int TPB, bool SEG>
 __global__ void __launch_bounds__(TPB)
 k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__ iin,
            const double* __restrict__ xin, const double* __restrict__ yin, const double* __restrict__ gin,
-           int shift, int nblk, const int32_t* __restrict__ offs, const int32_t* __restrict__ total,
-           Records out, float4* __restrict__ pk, const Inst* __restrict__ inst, int n_inst,
+           int shift, int nblk, const int32_t* __restrict__ hist, const int32_t* __restrict__ offs,
+           const int32_t* __restrict__ total, Records out, float4* __restrict__ pk, const Inst* __restrict__ inst, int n_inst,
            int key_shift, const int32_t* __restrict__ n_dev)
 {
     if (n_dev) n = *n_dev;
@@ -436,7 +449,12 @@ k_rscatter(int n, const uint32_t* __restrict__ kin, const uint32_t* __restrict__
         const int32_t* row = offs + int64_t(tid) * nblk;
         go = row[blk];
         tv = total[tid];
-        hv = (blk + 1 < nblk ? row[blk + 1] : tv) - go;
+        if (hist) {
+            hv = hist[int64_t(tid) * nblk + blk];
+        } else {
+            const int next = row[min(blk + 1, nblk - 1)];
+            hv = (blk + 1 < nblk ? next : tv) - go;
+        }
         if constexpr (SEG) {     // the instance's share of the row
             const int before = row[seg.t0];
             tv = (seg.t1 < nblk ? row[seg.t1] : tv) - before;
@@ -999,7 +1017,8 @@ constexpr int kWideTilesMax = 4096;
 
 void scan_table(const Buffers& b, int nblk, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_scan_rows, dim3(kRadixBins), dim3(kRowScanThreads), 0, st, nblk, b.hist, b.scan_part);
+    hipLaunchKernelGGL(k_scan_rows, dim3(kRadixBins), dim3(kRowScanThreads), 0, st, nblk, b.hist, b.hist_scan,
+                       b.scan_part);
 }
 
 }  // namespace
@@ -1017,6 +1036,7 @@ void radix_sort(const Buffers& b, int n, int nblk, bool wide, bool seg, int npas
                            : (wide ? k_rhist<1024, false> : k_rhist<256, false>);
     const auto scatter = seg ? (wide ? k_rscatter<1024, true> : k_rscatter<256, true>)
                              : (wide ? k_rscatter<1024, false> : k_rscatter<256, false>);
+    const int32_t* counts = b.hist_scan == b.hist ? nullptr : b.hist;
     const uint32_t* iin = nullptr;
     // the last pass writes the final arrays, the others alternate with tmp
     for (int pass = 0; pass < npass; ++pass) {
@@ -1026,8 +1046,8 @@ void radix_sort(const Buffers& b, int n, int nblk, bool wide, bool seg, int npas
             hipLaunchKernelGGL(count, dim3(nblk), dim3(threads), 0, st, n, kin, shift, nblk, b.hist, b.inst, b.n_inst,
                                n_dev);
         scan_table(b, nblk, st);
-        hipLaunchKernelGGL(scatter, dim3(nblk), dim3(threads), 0, st, n, kin, iin, xin, yin, gin, shift, nblk, b.hist,
-                           b.scan_part, out, pass == npass - 1 ? pk : nullptr, b.inst, b.n_inst,
+        hipLaunchKernelGGL(scatter, dim3(nblk), dim3(threads), 0, st, n, kin, iin, xin, yin, gin, shift, nblk, counts,
+                           b.hist_scan, b.scan_part, out, pass == npass - 1 ? pk : nullptr, b.inst, b.n_inst,
                            b.key_shift, n_dev);
         kin = out.k;
         iin = out.idx;
