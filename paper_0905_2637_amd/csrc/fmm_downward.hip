@@ -258,10 +258,11 @@ __device__ __forceinline__ void m2l_items_block(T* bx, T* by, const cplx<T>* __r
 // classes are the faster all the same).  M2L stage, pairs -> classes: 32 -> 29 us (P = 8),
 // 50 -> 43 (12), 86.5 -> 72 (17), 103 -> 78 (20), 139 -> 119 (24) at 1M
 // particles, depth 8; 1175 -> 778 at 16M, depth 10, P = 20; 39 -> 30 at 200k,
-// depth 6, P = 17.  At two wavefronts per SIMD it fills a quarter of the FP64
-// issue cycles at 1M particles (18 of 71 us) and half at 64M (1.55 of 3.1 ms);
-// the rest is waits: scalar loads of the data, one residue ahead, and the
-// stage.  One input term at a time (three wavefronts fit) reads each datum twice as often for
+// depth 6, P = 17.  At two wavefronts per SIMD its vector instructions fill a
+// third of the issue cycles at 1M particles (24 of 71 us, 18 of them these
+// multiply-adds and additions) and 0.57 at 64M (1.73 of 3.06 ms, 1.55); waits
+// for memory and LDS take 0.36 and 0.28 of the wavefronts' time (counters).  One
+// input term at a time (three wavefronts fit) reads each datum twice as often for
 // its product: 81 us at P = 17, 267 at 24.  Data residue by residue instead
 // of in order of n (below): 74 -> 72 at P = 17, 134 -> 119 at 24, 824 -> 778
 // at 16M.
